@@ -382,10 +382,10 @@ int64_t scone_discover_workspace(int64_t B, int64_t T, int32_t max_len);
  *     F(w) = LNf(h_{n-1})
  * with causal multi-head attention (scores scaled by 1/sqrt(d / n_heads)),
  * exact erf GELU, LayerNorm epsilon 1e-5 over the population variance, and
- * y = x W^T + b for every linear map (W stored [out, in]).  F-grams of equal
- * length are processed together, unpadded (the paper right-pads a batch to
- * its longest f-gram; under causal attention the final token never sees a
- * pad, so the result is the same).
+ * y = x W^T + b for every linear map (W stored [out, in]).  Nothing is padded
+ * (the paper right-pads a batch to its longest f-gram; under causal attention
+ * the final token never sees a pad, so the result is the same), and the states
+ * of a prefix that several f-grams share are computed once.
  *
  *  fgrams    [n, max_len] int32, row k = f-gram k oldest first (entries past
  *            lengths[k] are ignored); tokens in [0, vocab) else SCONE_ETOKEN.
@@ -413,14 +413,34 @@ int64_t scone_discover_workspace(int64_t B, int64_t T, int32_t max_len);
  * tok_rows, params and rows must be 16-byte aligned (else SCONE_EINVAL).
  * Synchronous: returns after the rows are written, with the first data error
  * (SCONE_ELEN, SCONE_ETOKEN, SCONE_EROW) or SCONE_OK.  Allocates and frees its
- * own device scratch: about 65536 * (14 d + 2 d_ff) bytes of activations for
- * one chunk of same-length f-grams, plus 4 n bytes.
+ * own device scratch of scone_fgram_model_workspace bytes: about 65536 *
+ * (12 d + 2 d_ff) for the activations of one chunk of f-grams (less when n *
+ * max_len is below 65536), plus about 19 n.
  */
 int scone_fgram_model_forward(const int32_t* fgrams, const int32_t* lengths,
                               const int32_t* row_ids, int64_t n, int32_t max_len,
                               const void* tok_rows, int64_t vocab, const void* params, int32_t d,
                               int32_t n_heads, int32_t d_ff, int32_t n_layers, void* rows,
                               int64_t n_rows, void* stream);
+
+/*
+ * scone_fgram_model_forward in the caller's scratch: `workspace` is device
+ * memory of at least scone_fgram_model_workspace bytes, 256-byte aligned, that
+ * shares memory with no other argument (else SCONE_EINVAL), reusable as soon as
+ * the call returns; NULL makes the call allocate it.  Programs that precompute
+ * rows often save an allocation of hundreds of megabytes per call.
+ */
+int scone_fgram_model_forward_in(const int32_t* fgrams, const int32_t* lengths,
+                                 const int32_t* row_ids, int64_t n, int32_t max_len,
+                                 const void* tok_rows, int64_t vocab, const void* params,
+                                 int32_t d, int32_t n_heads, int32_t d_ff, int32_t n_layers,
+                                 void* rows, int64_t n_rows, void* workspace,
+                                 int64_t workspace_bytes, void* stream);
+
+/* Bytes of workspace scone_fgram_model_forward_in needs, or -1 for sizes that
+ * the call rejects. */
+int64_t scone_fgram_model_workspace(int64_t n, int32_t max_len, int32_t d, int32_t n_heads,
+                                    int32_t d_ff);
 
 /*
  * Packing of scone_fgram_model_forward's parameters: offsets[k] (elements)

@@ -69,6 +69,11 @@ def _declare(L):
     L.scone_fgram_model_forward.argtypes = [P, P, P, I64, I32, P, I64, P, I32, I32, I32, I32,
                                             P, I64, P]
     L.scone_fgram_model_forward.restype = I
+    L.scone_fgram_model_forward_in.argtypes = [P, P, P, I64, I32, P, I64, P, I32, I32, I32, I32,
+                                               P, I64, P, I64, P]
+    L.scone_fgram_model_forward_in.restype = I
+    L.scone_fgram_model_workspace.argtypes = [I64, I32, I32, I32, I32]
+    L.scone_fgram_model_workspace.restype = I64
     L.scone_fgram_model_layout.argtypes = [I32, I32, I32, I32, I32, ctypes.POINTER(I64),
                                            ctypes.POINTER(I64), ctypes.POINTER(I64)]
     L.scone_fgram_model_layout.restype = I
@@ -110,6 +115,22 @@ def _stream(stream) -> Optional[int]:
     if stream is None:
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _scratch(nbytes: int, device: torch.device, stream) -> Optional[torch.Tensor]:
+    """Device scratch from torch's caching allocator, ordered on the stream that
+    the call runs on (a block given back by another stream's work may still be
+    in use there); None when the allocator has no memory left, and the library
+    then tries for itself."""
+    try:
+        if stream is None:
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        if not isinstance(stream, torch.cuda.Stream):
+            stream = torch.cuda.ExternalStream(_stream(stream), device=device)
+        with torch.cuda.stream(stream):
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
 
 
 def _dev_i32(t: torch.Tensor, name: str, ndim: Optional[int] = None) -> torch.Tensor:
@@ -345,10 +366,14 @@ def precompute_fgram_rows(model: FgramModel, fgrams: torch.Tensor, lengths: torc
     if K != model.max_len or lengths.numel() != n or row_ids.numel() != n:
         raise ValueError("fgrams must be [n, max_len] with n lengths and n row ids")
     with torch.cuda.device(rows.device):
-        rc = lib().scone_fgram_model_forward(
+        need = lib().scone_fgram_model_workspace(n, model.max_len, model.d, model.n_heads,
+                                                 model.d_ff)
+        work = _scratch(need, rows.device, stream) if n > 0 and need > 0 else None
+        rc = lib().scone_fgram_model_forward_in(
             _ptr(fgrams), _ptr(lengths), _ptr(row_ids), n, model.max_len, _ptr(tok_rows),
             tok_rows.shape[0], model.blob.data_ptr(), model.d, model.n_heads, model.d_ff,
-            model.n_layers, _ptr(rows), rows.shape[0], _stream(stream))
+            model.n_layers, _ptr(rows), rows.shape[0], _ptr(work),
+            0 if work is None else work.numel(), _stream(stream))
     _check(rc, "scone_fgram_model_forward")
     return rows
 

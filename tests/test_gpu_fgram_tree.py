@@ -1,0 +1,98 @@
+"""The precompute's prefix tree (csrc/fgram_tree.h): f-grams that share prefixes,
+in one chunk and in several, sorted by ranks or by radix passes.
+
+The oracle computes every f-gram on its own; the bound is that of
+test_gpu_fgram_model.py.
+"""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2502_01637_amd as S
+from oracle import fgram_model as orc
+from workloads.fgram_model import ModelConfig, make_params, make_token_rows, bf16_bits_to_f64
+from gpu_util import dev
+from test_gpu_fgram_model import as_f64, assert_close, bf16_dev, random_fgrams, run
+
+# (n, vocabulary, K): one f-gram; prefixes that nearly all share, duplicates
+# among them; the largest rank sort and the smallest radix sort; key values of
+# one, two and three bytes; one prefix group over several chunks; many chunks
+CASES = [(1, 5, 7), (3000, 2, 7), (8192, 300, 5), (8193, 300, 5), (9000, 255, 3),
+         (9000, 256, 6), (9000, 65535, 3), (9000, 65536, 3), (9000, 70000, 4),
+         (150_000, 1, 2), (70_001, 30, 4), (120_000, 3000, 3)]
+
+
+def pytest_id(c):
+    return "n%d_V%d_K%d" % c
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES, ids=pytest_id)
+def test_shared_prefixes(case):
+    n, V, K = case
+    cfg = ModelConfig(512, 8, 128, 1, K)
+    rng = np.random.default_rng(n + V + K)
+    P = make_params(cfg, seed=1)
+    T = make_token_rows(V, cfg.d, seed=2)
+    fg, lengths = random_fgrams(rng, V, n, K)
+    fg[lengths == K, 0] = V - 1                      # a large group with one first token
+    ids = rng.permutation(n).astype(np.int32)
+    got = run(cfg, fg, lengths, ids, T, P, n)
+    # the ends of the sorted order and of the input, and a random sample
+    order = np.lexsort(fg.T[::-1])
+    pick = np.unique(np.concatenate([order[:20], order[-20:], order[n // 2:n // 2 + 20],
+                                     [0, n - 1], rng.integers(0, n, 100)]))
+    ref = orc.forward(fg[pick], lengths[pick], bf16_bits_to_f64(T),
+                      {k: bf16_bits_to_f64(v) for k, v in P.items()}, 1, 8)
+    assert_close(as_f64(got[torch.from_numpy(ids[pick].astype(np.int64)).cuda()]), ref, 1)
+    # the same bits as in a call of their own (another sort, other neighbours)
+    alone = run(cfg, fg[pick], lengths[pick], np.arange(len(pick), dtype=np.int32), T, P,
+                len(pick))
+    assert torch.equal(alone.view(torch.int16),
+                       got[torch.from_numpy(ids[pick].astype(np.int64)).cuda()].view(torch.int16))
+
+
+@pytest.mark.gpu
+def test_workspace_argument():
+    """The C call in the caller's scratch: the same rows; a short, misaligned or
+    overlapping workspace is refused."""
+    cfg = ModelConfig(512, 8, 256, 2, 3)
+    rng = np.random.default_rng(3)
+    V, n = 100, 500
+    P, T = make_params(cfg, seed=5), make_token_rows(V, cfg.d, seed=6)
+    fg, lengths = random_fgrams(rng, V, n, 3)
+    ids = np.arange(n, dtype=np.int32)
+    want = run(cfg, fg, lengths, ids, T, P, n)
+    model = S.FgramModel(P, cfg.d, cfg.n_heads, cfg.d_ff, cfg.n_layers, 3)
+    L = S.scone.lib()
+    need = L.scone_fgram_model_workspace(n, 3, cfg.d, cfg.n_heads, cfg.d_ff)
+    t = [dev(fg), dev(lengths), dev(ids), bf16_dev(T), torch.zeros_like(want),
+         torch.empty(need + 512, dtype=torch.uint8, device="cuda")]
+    st = torch.cuda.current_stream().cuda_stream
+
+    def call(ws, nbytes, rows=t[4]):
+        return L.scone_fgram_model_forward_in(
+            t[0].data_ptr(), t[1].data_ptr(), t[2].data_ptr(), n, 3, t[3].data_ptr(), V,
+            model.blob.data_ptr(), cfg.d, cfg.n_heads, cfg.d_ff, cfg.n_layers, rows.data_ptr(), n,
+            ctypes.c_void_p(ws), nbytes, st)
+
+    for ws, nbytes in [(t[5].data_ptr(), need), (None, 0)]:
+        t[4].zero_()
+        assert call(ws, nbytes) == S.scone.OK
+        assert torch.equal(t[4].view(torch.int16), want.view(torch.int16))
+    assert call(t[5].data_ptr(), need - 1) == S.scone.EINVAL
+    assert call(t[5].data_ptr() + 16, need) == S.scone.EINVAL
+    assert call(t[4].data_ptr(), need) == S.scone.EINVAL
+
+
+def test_workspace_sizes():
+    L = S.scone.lib()
+    w = L.scone_fgram_model_workspace
+    assert w(1000, 3, 500, 8, 512) == -1 and w(-1, 3, 512, 8, 512) == -1
+    assert w(1000, 8, 512, 8, 512) == -1 and w(1 << 31, 3, 512, 8, 512) == -1
+    # activations of 3,000 rows, and of a whole chunk however many f-grams follow
+    assert 3000 * (12 * 512 + 2 * 512) <= w(1000, 3, 512, 8, 512) <= 3300 * (12 * 512 + 1024)
+    big = w(1_000_000, 3, 1024, 16, 4096)
+    assert 0 < big - 65536 * (12 * 1024 + 2 * 4096) <= 25 * 1_000_000
