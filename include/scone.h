@@ -102,6 +102,25 @@ int scone_build_fgram_table(const int32_t* fgrams, const int32_t* lengths,
                             double max_load, void* stream, scone_table_t** out);
 
 /*
+ * scone_build_fgram_table in the caller's memory: `memory` is device memory of
+ * at least scone_fgram_table_bytes for the same lengths and load, 256-byte
+ * aligned, that shares memory with no input (else SCONE_EINVAL).  It holds the
+ * dictionary until scone_table_destroy, which does not free it.  A program that
+ * keeps its own pool of device memory saves an allocation of up to gigabytes
+ * per table.
+ */
+int scone_build_fgram_table_in(const int32_t* fgrams, const int32_t* lengths,
+                               const int32_t* ids, int64_t n, int32_t max_len,
+                               double max_load, void* memory, int64_t memory_bytes,
+                               void* stream, scone_table_t** out);
+
+/* *bytes (host) receives the device memory that the dictionary of these lengths
+ * takes.  scratch: 256 bytes of device memory, 256-byte aligned, to count in.
+ * Synchronous on `stream`. */
+int scone_fgram_table_bytes(const int32_t* lengths, int64_t n, int32_t max_len, double max_load,
+                            void* scratch, void* stream, int64_t* bytes);
+
+/*
  * Longest-suffix lookup (Algorithm 1, the choice of j): for every b < B and
  * t < T, fgram_ids[b,t] is the id of the longest f-gram
  * (X[b,t-n+1], ..., X[b,t]) with 2 <= n <= min(max_n, t+1) that is in the

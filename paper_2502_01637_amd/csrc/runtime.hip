@@ -109,7 +109,7 @@ void scone_table_destroy(scone_table_t* t) {
     int cur = 0;
     const bool have_cur = hipGetDevice(&cur) == hipSuccess;
     if (have_cur && cur != t->device) (void)hipSetDevice(t->device);
-    if (t->slots) (void)hipFree(t->slots);
+    if (t->owned) (void)hipFree(t->owned);
     if (have_cur && cur != t->device) (void)hipSetDevice(cur);
     delete t;
 }

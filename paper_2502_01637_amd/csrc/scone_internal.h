@@ -138,7 +138,8 @@ struct alignas(32) Slot32 {
     uint64_t w0;
     uint64_t w1;
     int32_t id;
-    int32_t pad[3];
+    uint32_t ready;  // used while the table is built (SlotOps<32>)
+    int32_t pad[2];
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -160,9 +161,14 @@ struct SlotOps<16> {
     }
     __device__ __forceinline__ static void write_rest(Slot16* base, uint64_t s, const Key& k,
                                                       int32_t id) {
-        base[s].w1 = (uint32_t)k.w1;
-        base[s].id = id;
+        *reinterpret_cast<u32x2*>(&base[s].w1) = u32x2{(uint32_t)k.w1, (uint32_t)id};
     }
+    // Keys of 3 tokens are whole in their first word; no other is compared
+    // while a table of 16-byte slots is built (SlotOps<32> has the other case).
+    __device__ __forceinline__ static uint32_t load_ready(const Slot16*, uint64_t) { return 1; }
+    __device__ __forceinline__ static void publish_w1(Slot16*, uint64_t, uint64_t) {}
+    __device__ __forceinline__ static bool ready_now(Slot16*, uint64_t) { return true; }
+    __device__ __forceinline__ static bool same_w1(Slot16*, uint64_t, uint64_t) { return true; }
 };
 
 template <>
@@ -180,6 +186,29 @@ struct SlotOps<32> {
                                                       int32_t id) {
         base[s].w1 = k.w1;
         base[s].id = id;
+        base[s].ready = 1;
+    }
+    // For builders that compare keys while others write them: `ready` is set
+    // once w1 is in place.
+    __device__ __forceinline__ static uint32_t load_ready(const Slot32* base, uint64_t s) {
+        const uint32_t r = __hip_atomic_load(&base[s].ready, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WAVEFRONT);
+        asm volatile("" ::"v"(r) : "memory");  // has returned before any later load
+        return r;
+    }
+    __device__ __forceinline__ static void publish_w1(Slot32* base, uint64_t s, uint64_t w1) {
+        const unsigned long long old =
+            atomicExch(reinterpret_cast<unsigned long long*>(&base[s].w1), (unsigned long long)w1);
+        uint32_t one = 1;
+        asm volatile("" : "+v"(one) : "v"(old) : "memory");  // w1 has been written
+        atomicExch(&base[s].ready, one);
+    }
+    __device__ __forceinline__ static bool ready_now(Slot32* base, uint64_t s) {
+        return atomicOr(&base[s].ready, 0u) != 0;
+    }
+    __device__ __forceinline__ static bool same_w1(Slot32* base, uint64_t s, uint64_t w1) {
+        if (!ready_now(base, s)) return false;
+        return atomicOr(reinterpret_cast<unsigned long long*>(&base[s].w1), 0ull) == w1;
     }
 };
 
@@ -281,4 +310,5 @@ struct scone_table {
     int64_t capacity;   // slots, a power of two
     int64_t entries;    // slots in use: the f-grams plus their suffix markers
     void* slots;        // device memory, capacity * slot_bytes
+    void* owned = nullptr;  // what scone_table_destroy frees: the slots, unless the caller's
 };

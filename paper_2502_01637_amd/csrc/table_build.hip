@@ -5,11 +5,12 @@
 // (Section 3.2).  Here the dictionary is a power-of-two array of slots with
 // linear probing from the start of the key's 64-byte bucket.  Insertion
 // claims the first empty slot on the key's probe path with a 64-bit
-// compare-and-swap on the slot's first key word, then
-// writes the rest of the key and the id; it never compares keys, so slot
-// placement under concurrency does not matter.  A second pass re-probes every
-// input key: the first slot holding that key must be the one its own thread
-// claimed, otherwise the key was inserted twice (a duplicate f-gram).
+// compare-and-swap on the slot's first key word, then writes the rest of the
+// key and the id.  Two f-grams with one key walk the same path, so the second
+// one meets the first one's slot: a compare-and-swap that finds the key's own
+// first word makes the key a suspect, and only where there are suspects does a
+// second pass read every key's path and report a key that stands in it twice
+// (a duplicate f-gram).
 //
 // A third pass adds the suffix entries that let lookups skip probes: for
 // every f-gram of length 4 or more, the entry of its last three tokens gets
@@ -19,8 +20,15 @@
 // at once, leaving two identical copies; lookups read whichever comes first
 // on the probe path, so that costs a slot and nothing else.  The slot count
 // allows for one marker per such suffix.
+//
+// All of it is random 128-byte lines of the table: 10M f-grams of length 2-5
+// (a table of 1 GB) take 807 us to insert and 590 us to mark on MI355X.  The
+// passes use read-modify-writes and plain loads only: a marking pass that
+// published its slots with agent-scope release and acquire, which write back
+// and invalidate the whole L2, took 7.3 ms.
 #include <algorithm>
 #include <cmath>
+#include <new>
 
 #include "scone_internal.h"
 
@@ -40,11 +48,10 @@ template <int SB>
 __global__ __launch_bounds__(kBuildThreads) void k_insert(
     const int32_t* __restrict__ fgrams, const int32_t* __restrict__ lengths,
     const int32_t* __restrict__ ids, int64_t n, int max_len,
-    typename SlotOps<SB>::Slot* __restrict__ slots, uint64_t mask,
-    int64_t* __restrict__ slot_of, unsigned* __restrict__ status, int64_t block0) {
+    typename SlotOps<SB>::Slot* __restrict__ slots, uint64_t mask, unsigned* __restrict__ status,
+    unsigned* __restrict__ suspects, int64_t block0) {
     const int64_t k = block_index(block0) * kBuildThreads + threadIdx.x;
     if (k >= n) return;
-    slot_of[k] = -1;
     const int len = lengths[k];
     const int32_t id = ids[k];
     if (len < 2 || len > max_len) {
@@ -64,173 +71,264 @@ __global__ __launch_bounds__(kBuildThreads) void k_insert(
     uint64_t s = home_slot(key, mask, Bucket<SB>::kSlots);
     for (uint64_t step = 0; step <= mask; ++step) {
         unsigned long long* w0 = reinterpret_cast<unsigned long long*>(&slots[s].w0);
-        if (atomicCAS(w0, 0ull, (unsigned long long)key.w0) == 0ull) {
+        const uint64_t old = atomicCAS(w0, 0ull, (unsigned long long)key.w0);
+        if (old == 0) {
             SlotOps<SB>::write_rest(slots, s, key, id);
-            slot_of[k] = (int64_t)s;
             return;
         }
+        if (old == key.w0) atomicOr(suspects, 1u);
         s = (s + 1) & mask;
     }
     atomicOr(status, err_bit(SCONE_EFULL));
 }
+
+// Reports keys that stand twice in their probe path (a path ends at its first
+// empty slot).  Runs only where the insertion met a suspect and every input
+// was in range (an input error comes first, and leaves keys out of the table).
+constexpr int kSweepBlocks = 2048;  // workgroups of the passes that take runs of f-grams
+constexpr int kCountBlocks = 512;   // of the count, whose adds to one word are serialised
 
 template <int SB>
 __global__ __launch_bounds__(kBuildThreads) void k_verify(
     const int32_t* __restrict__ fgrams, const int32_t* __restrict__ lengths, int64_t n,
     int max_len, const typename SlotOps<SB>::Slot* __restrict__ slots, uint64_t mask,
-    const int64_t* __restrict__ slot_of, unsigned* __restrict__ status, int64_t block0) {
-    const int64_t k = block_index(block0) * kBuildThreads + threadIdx.x;
-    if (k >= n) return;
-    const int64_t mine = slot_of[k];
-    if (mine < 0) return;  // rejected or not placed: already reported
-    const Key key = pack_key(fgrams + k * (int64_t)max_len, lengths[k]);
-    uint64_t s = home_slot(key, mask, Bucket<SB>::kSlots);
-    for (uint64_t step = 0; step <= mask; ++step) {
-        uint64_t w0, w1;
-        int32_t id;
-        SlotOps<SB>::read(slots, s, w0, w1, id);
-        if (w0 == key.w0 && w1 == key.w1) {
-            if ((int64_t)s != mine) atomicOr(status, err_bit(SCONE_EDUP));
-            return;
+    unsigned* __restrict__ status, const unsigned* __restrict__ suspects) {
+    if (*suspects == 0) return;
+    if (__hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
+        (err_bit(SCONE_ELEN) | err_bit(SCONE_EID) | err_bit(SCONE_ETOKEN) | err_bit(SCONE_EFULL)))
+        return;
+    for (int64_t k = (int64_t)blockIdx.x * kBuildThreads + threadIdx.x; k < n;
+         k += (int64_t)gridDim.x * kBuildThreads) {
+        const Key key = pack_key(fgrams + k * (int64_t)max_len, lengths[k]);
+        uint64_t s = home_slot(key, mask, Bucket<SB>::kSlots);
+        int found = 0;
+        for (uint64_t step = 0; step <= mask && found < 2; ++step) {
+            uint64_t w0, w1;
+            int32_t id;
+            SlotOps<SB>::read(slots, s, w0, w1, id);
+            if (w0 == 0) break;
+            found += w0 == key.w0 && w1 == key.w1 ? 1 : 0;
+            s = (s + 1) & mask;
         }
-        if (w0 == 0) break;
-        s = (s + 1) & mask;
+        if (found > 1) atomicOr(status, err_bit(SCONE_EDUP));
     }
-    // Its own slot lies on its probe path, so reaching here is a broken table.
-    atomicOr(status, err_bit(SCONE_EFULL));
 }
 
-// Counts the f-grams of length 4..max_len and 6..max_len (the suffix
-// entries the third pass may add).
+// Counts the f-grams of length 4..max_len and 6..max_len (the suffix entries
+// the third pass may add).  Each workgroup takes a strided run of the lengths
+// and adds each count once: with one workgroup per 256 lengths, the adds to
+// the two counters were serialised and took 472 us for 10M f-grams instead of
+// 17 us.
 __global__ __launch_bounds__(kBuildThreads) void k_count_long(
     const int32_t* __restrict__ lengths, int64_t n, int max_len,
-    unsigned long long* __restrict__ counts, int64_t block0) {
+    unsigned long long* __restrict__ counts) {
     __shared__ unsigned s_c[2];
     if (threadIdx.x < 2) s_c[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t k = block_index(block0) * kBuildThreads + threadIdx.x;
-    const int len = k < n ? lengths[k] : 0;
-    const unsigned c4 = (unsigned)__popcll(__ballot(len >= 4 && len <= max_len));
-    const unsigned c6 = (unsigned)__popcll(__ballot(len >= 6 && len <= max_len));
-    if ((threadIdx.x & 63) == 0) {
-        if (c4) atomicAdd(&s_c[0], c4);
-        if (c6) atomicAdd(&s_c[1], c6);
+    unsigned c4 = 0, c6 = 0;
+    const int64_t stride = (int64_t)gridDim.x * kBuildThreads;
+    for (int64_t k = (int64_t)blockIdx.x * kBuildThreads + threadIdx.x; k < n; k += 8 * stride) {
+        int len[8];  // eight loads in flight
+#pragma unroll
+        for (int u = 0; u < 8; ++u) len[u] = k + u * stride < n ? lengths[k + u * stride] : 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            c4 += len[u] >= 4 && len[u] <= max_len ? 1u : 0u;
+            c6 += len[u] >= 6 && len[u] <= max_len ? 1u : 0u;
+        }
     }
+    if (c4) atomicAdd(&s_c[0], c4);
+    if (c6) atomicAdd(&s_c[1], c6);
     __syncthreads();
-    // one global add per workgroup and counter (same-address atomics serialise)
     if (threadIdx.x < 2 && s_c[threadIdx.x])
         atomicAdd(counts + threadIdx.x, (unsigned long long)s_c[threadIdx.x]);
 }
 
-// Counts the slots in use (f-grams and suffix markers, non-zero first key
-// word) after a build: kUsedPer slots per thread, one global add per workgroup.
-constexpr int kUsedPer = 16;
+// Gives the entry of `key` (3 or 5 tokens) kExtBit, inserting a marker when the
+// key has no entry; returns whether it inserted one.
+//
+// A plain look comes first: most suffixes that many f-grams share are found
+// with the bit set, from the L2.  Plain loads may be older than other
+// workgroups' writes, so what they don't show is settled with
+// read-modify-writes.  A length-3 key is whole in its first word (52 bits; the
+// second is 0), so one compare-and-swap claims or finds its slot.  A length-5
+// key has 20 bits in the second word: the claimer writes that word and then
+// `ready`, each with a read-modify-write that has returned before the next, and
+// others compare the second word only once they have seen `ready`; a slot that
+// is not ready counts as another key (at worst a second, identical marker).
+// The id word of a marker is written with an atomic OR of all its bits, since
+// another thread may set kExtBit at the same time.
+constexpr int kMaxLooks = 256;
 
-template <int SB>
-__global__ __launch_bounds__(kBuildThreads) void k_count_used(
-    const typename SlotOps<SB>::Slot* __restrict__ slots, int64_t cap,
-    unsigned long long* __restrict__ used, int64_t block0) {
-    __shared__ unsigned s_c;
-    if (threadIdx.x == 0) s_c = 0;
-    __syncthreads();
-    const int64_t base = block_index(block0) * (kBuildThreads * kUsedPer) + threadIdx.x;
-    unsigned c = 0;
-#pragma unroll
-    for (int i = 0; i < kUsedPer; ++i) {
-        const int64_t k = base + (int64_t)i * kBuildThreads;
-        if (k < cap && slots[k].w0 != 0) ++c;
-    }
-    for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off);
-    if ((threadIdx.x & 63) == 0 && c) atomicAdd(&s_c, c);
-    __syncthreads();
-    if (threadIdx.x == 0 && s_c) atomicAdd(used, (unsigned long long)s_c);
-}
-
-// Gives the entry of `key` kExtBit, inserting a marker when the key has no
-// entry.  A marker slot is claimed in three steps: its first key word goes
-// from 0 to kBusy (no key has length field 15), the rest of the key and the
-// id are written, and only then is the first word set to the key with
-// release order.  A thread that reads its key in the first word and then
-// takes an acquire fence therefore also sees that key's second word, so it
-// never takes a half-written slot for its own key; a slot still kBusy counts
-// as another key (at worst a second, identical marker).
-constexpr uint64_t kBusy = 0xF;
-
-template <int SB>
-__device__ __forceinline__ void mark_suffix(typename SlotOps<SB>::Slot* slots, uint64_t mask,
+template <int SB, int kTokens>
+__device__ __forceinline__ bool mark_suffix(typename SlotOps<SB>::Slot* slots, uint64_t mask,
                                             const Key& key, unsigned* status) {
-    uint64_t s = home_slot(key, mask, Bucket<SB>::kSlots);
-    for (uint64_t step = 0; step <= mask; ++step) {
-        unsigned long long* w0p = reinterpret_cast<unsigned long long*>(&slots[s].w0);
-        uint64_t w0 = __hip_atomic_load(w0p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (w0 == 0) {
-            w0 = atomicCAS(w0p, 0ull, (unsigned long long)kBusy);
-            if (w0 == 0) {
-                SlotOps<SB>::write_rest(slots, s, key, (int32_t)(kMarkerId | kExtBit));
-                __hip_atomic_store(w0p, (unsigned long long)key.w0, __ATOMIC_RELEASE,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-                return;
-            }
-            w0 = __hip_atomic_load(w0p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    static_assert(kTokens == 3 || (kTokens == 5 && SB == 32), "suffixes of 3 or 5 tokens");
+    constexpr int BW = Bucket<SB>::kSlots;
+    const uint64_t home = home_slot(key, mask, BW);
+    // an entry's ready word is read before its key words, so that these are whole
+#pragma unroll
+    for (int i = 0; i < BW; ++i) {
+        if (kTokens == 5) {
+            const uint32_t ready = SlotOps<SB>::load_ready(slots, home + i);
+            if (!ready) continue;
         }
-        if (w0 == key.w0) {
-            // the release store that published this key word happened before:
-            // an acquire fence makes the rest of the slot visible
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            uint64_t w1;
-            if (SB == 16)
-                w1 = __hip_atomic_load(reinterpret_cast<uint32_t*>(&slots[s]) + 2,
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            else
-                w1 = __hip_atomic_load(reinterpret_cast<unsigned long long*>(&slots[s]) + 1,
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (w1 == key.w1) {
-                // common suffixes end many f-grams: skip the atomic once the bit is set
-                unsigned* idp = reinterpret_cast<unsigned*>(&slots[s].id);
-                if (!(__hip_atomic_load(idp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
-                      kExtBit))
-                    atomicOr(idp, kExtBit);
-                return;
+        uint64_t w0, w1;
+        int32_t id;
+        SlotOps<SB>::read(slots, home + i, w0, w1, id);
+        if (w0 == key.w0 && w1 == key.w1 && id < 0) return false;
+    }
+    uint64_t s = home;
+    int looks = 0;
+    for (uint64_t step = 0; step <= mask;) {
+        const uint64_t old =
+            atomicCAS(reinterpret_cast<unsigned long long*>(&slots[s].w0), 0ull,
+                      (unsigned long long)key.w0);
+        unsigned* idp = reinterpret_cast<unsigned*>(&slots[s].id);
+        if (old == 0) {
+            if (kTokens == 5) SlotOps<SB>::publish_w1(slots, s, key.w1);
+            atomicOr(idp, (unsigned)kMarkerId | kExtBit);
+            return true;
+        }
+        if (old == key.w0) {
+            if (kTokens == 5 && !SlotOps<SB>::ready_now(slots, s) && ++looks < kMaxLooks) continue;
+            if (kTokens == 3 || SlotOps<SB>::same_w1(slots, s, key.w1)) {
+                atomicOr(idp, kExtBit);
+                return false;
             }
         }
         s = (s + 1) & mask;
+        ++step;
     }
     atomicOr(status, err_bit(SCONE_EFULL));
+    return false;
 }
 
+// Marks every suffix and counts the markers inserted (one add per workgroup).
+// Skipped when an input was rejected: the table is given up then.
 template <int SB>
 __global__ __launch_bounds__(kBuildThreads) void k_mark(
     const int32_t* __restrict__ fgrams, const int32_t* __restrict__ lengths, int64_t n,
-    int max_len, typename SlotOps<SB>::Slot* __restrict__ slots, uint64_t mask,
-    const int64_t* __restrict__ slot_of, unsigned* __restrict__ status, int64_t block0) {
-    const int64_t k = block_index(block0) * kBuildThreads + threadIdx.x;
-    if (k >= n || slot_of[k] < 0) return;  // rejected f-grams were reported
-    const int len = lengths[k];
-    const int32_t* tok = fgrams + k * (int64_t)max_len;
-    if (len >= 4) mark_suffix<SB>(slots, mask, pack_key(tok + len - 3, 3), status);
-    if (len >= 6) mark_suffix<SB>(slots, mask, pack_key(tok + len - 5, 5), status);
+    int max_len, typename SlotOps<SB>::Slot* __restrict__ slots, uint64_t mask, unsigned* status,
+    unsigned long long* __restrict__ markers) {
+    __shared__ unsigned s_c;
+    if (threadIdx.x == 0) s_c = 0;
+    __syncthreads();
+    unsigned c = 0;
+    if (__hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+        for (int64_t k = (int64_t)blockIdx.x * kBuildThreads + threadIdx.x; k < n;
+             k += (int64_t)gridDim.x * kBuildThreads) {
+            const int len = lengths[k];
+            const int32_t* tok = fgrams + k * (int64_t)max_len;
+            if (len >= 4) c += mark_suffix<SB, 3>(slots, mask, pack_key(tok + len - 3, 3), status);
+            if constexpr (SB == 32)
+                if (len >= 6)
+                    c += mark_suffix<SB, 5>(slots, mask, pack_key(tok + len - 5, 5), status);
+        }
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off);
+    if ((threadIdx.x & 63) == 0 && c) atomicAdd(&s_c, c);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_c) atomicAdd(markers, (unsigned long long)s_c);
 }
+
+// The build's control words, before the slots in a caller's memory.
+struct Control {
+    unsigned status;             // err_bit of every data error found
+    unsigned suspects;           // an insertion met its own first word
+    unsigned long long long4;    // f-grams of length 4 or more, and of 6 or more
+    unsigned long long long6;
+    unsigned long long markers;  // suffix markers inserted
+};
+constexpr int64_t kControlBytes = 256;
 
 template <int SB>
 hipError_t launch_build(const int32_t* fgrams, const int32_t* lengths, const int32_t* ids,
-                        int64_t n, int max_len, void* slots, uint64_t mask, int64_t* slot_of,
-                        unsigned* status, hipStream_t st) {
+                        int64_t n, int max_len, void* slots, uint64_t mask, Control* ctl,
+                        hipStream_t st) {
     using Slot = typename SlotOps<SB>::Slot;
+    Slot* sl = static_cast<Slot*>(slots);
     const int64_t blocks = (n + kBuildThreads - 1) / kBuildThreads;
+    const dim3 sweep((unsigned)std::min<int64_t>(blocks, kSweepBlocks)), block(kBuildThreads);
     const hipError_t e = launch_blocks(blocks, kBuildThreads, [&](int64_t b0, dim3 grid) {
-        hipLaunchKernelGGL(k_insert<SB>, grid, dim3(kBuildThreads), 0, st, fgrams, lengths, ids,
-                           n, max_len, static_cast<Slot*>(slots), mask, slot_of, status, b0);
+        hipLaunchKernelGGL(k_insert<SB>, grid, block, 0, st, fgrams, lengths, ids, n, max_len, sl,
+                           mask, &ctl->status, &ctl->suspects, b0);
     });
     if (e != hipSuccess) return e;
-    const hipError_t e2 = launch_blocks(blocks, kBuildThreads, [&](int64_t b0, dim3 grid) {
-        hipLaunchKernelGGL(k_verify<SB>, grid, dim3(kBuildThreads), 0, st, fgrams, lengths, n,
-                           max_len, static_cast<const Slot*>(slots), mask, slot_of, status, b0);
-    });
-    if (e2 != hipSuccess || max_len < 4) return e2;
-    return launch_blocks(blocks, kBuildThreads, [&](int64_t b0, dim3 grid) {
-        hipLaunchKernelGGL(k_mark<SB>, grid, dim3(kBuildThreads), 0, st, fgrams, lengths, n,
-                           max_len, static_cast<Slot*>(slots), mask, slot_of, status, b0);
-    });
+    hipLaunchKernelGGL(k_verify<SB>, sweep, block, 0, st, fgrams, lengths, n, max_len, sl, mask,
+                       &ctl->status, &ctl->suspects);
+    if (max_len >= 4)
+        hipLaunchKernelGGL(k_mark<SB>, sweep, block, 0, st, fgrams, lengths, n, max_len, sl, mask,
+                           &ctl->status, &ctl->markers);
+    return hipGetLastError();
+}
+
+int slot_bytes_for(int max_len) { return max_len <= kMaxLenSlot16 ? 16 : 32; }
+
+int build_sizes_ok(int64_t n, int32_t max_len, double max_load) {
+    if (n < 0 || max_len < 2 || max_len > SCONE_MAX_FGRAM_LEN) return SCONE_EINVAL;
+    if (!(max_load > 0.0 && max_load <= 0.9)) return SCONE_EINVAL;
+    // At most n entries plus one suffix entry per f-gram of length >= 4 and
+    // one more per f-gram of length >= 6, so n * 3 bounds them.
+    if (std::ceil(3.0 * (double)n / max_load) > (double)(1ull << 40)) return SCONE_EINVAL;
+    return SCONE_OK;
+}
+
+// Slots for these lengths: the smallest power of two >= max(64, entries /
+// max_load).  Lengths of 4 and more are counted on the device, in `ctl` (zeroed
+// here); waits for the stream where there can be any.
+int count_slots(const int32_t* lengths, int64_t n, int32_t max_len, double max_load,
+                Control* ctl, hipStream_t st, uint64_t& cap) {
+    unsigned long long more[2] = {0, 0};
+    SCONE_HIP_TRY(hipMemsetAsync(ctl, 0, sizeof(Control), st));
+    if (n > 0 && max_len >= 4) {
+        const int64_t blocks = (n + kBuildThreads - 1) / kBuildThreads;
+        hipLaunchKernelGGL(k_count_long, dim3((unsigned)std::min<int64_t>(blocks, kCountBlocks)),
+                           dim3(kBuildThreads), 0, st, lengths, n, (int)max_len, &ctl->long4);
+        SCONE_HIP_TRY(hipGetLastError());
+        SCONE_HIP_TRY(hipMemcpyAsync(more, &ctl->long4, sizeof(more), hipMemcpyDeviceToHost, st));
+        SCONE_HIP_TRY(hipStreamSynchronize(st));
+    }
+    const double entries = (double)n + (double)more[0] + (double)more[1];
+    const double want = std::max(64.0, std::ceil(entries / max_load));
+    cap = 64;
+    while ((double)cap < want) cap <<= 1;
+    return SCONE_OK;
+}
+
+// Fills a table of `cap` slots in `slots` and makes its handle; waits for the
+// stream.
+int fill_table(const int32_t* fgrams, const int32_t* lengths, const int32_t* ids, int64_t n,
+               int32_t max_len, void* slots, uint64_t cap, Control* ctl, int dev, hipStream_t st,
+               scone_table_t** out) {
+    const int slot_bytes = slot_bytes_for(max_len);
+    SCONE_HIP_TRY(hipMemsetAsync(slots, 0, cap * (uint64_t)slot_bytes, st));
+    if (n > 0) {
+        const hipError_t e =
+            slot_bytes == 16
+                ? launch_build<16>(fgrams, lengths, ids, n, max_len, slots, cap - 1, ctl, st)
+                : launch_build<32>(fgrams, lengths, ids, n, max_len, slots, cap - 1, ctl, st);
+        if (e != hipSuccess) return SCONE_EHIP;
+    }
+    Control h{};
+    SCONE_HIP_TRY(hipMemcpyAsync(&h, ctl, sizeof(h), hipMemcpyDeviceToHost, st));
+    SCONE_HIP_TRY(hipStreamSynchronize(st));
+    if (h.status) {
+        // Report argument-like data errors before structural ones.
+        for (int c : {SCONE_ELEN, SCONE_EID, SCONE_ETOKEN, SCONE_EDUP, SCONE_EFULL})
+            if (h.status & err_bit(c)) return c;
+        return SCONE_EFULL;
+    }
+    scone_table* t = new (std::nothrow) scone_table();
+    if (!t) return SCONE_ENOMEM;
+    t->device = dev;
+    t->max_len = max_len;
+    t->slot_bytes = slot_bytes;
+    t->n = n;
+    t->capacity = (int64_t)cap;
+    t->entries = n + (int64_t)h.markers;
+    t->slots = slots;
+    *out = t;
+    return SCONE_OK;
 }
 
 }  // namespace
@@ -242,137 +340,79 @@ extern "C" int scone_build_fgram_table(const int32_t* fgrams, const int32_t* len
     using namespace scone;
     if (!out) return SCONE_EINVAL;
     *out = nullptr;
-    if (n < 0 || max_len < 2 || max_len > SCONE_MAX_FGRAM_LEN) return SCONE_EINVAL;
-    if (!(max_load > 0.0 && max_load <= 0.9)) return SCONE_EINVAL;
+    int rc = build_sizes_ok(n, max_len, max_load);
+    if (rc != SCONE_OK) return rc;
     if (n > 0 && (!fgrams || !lengths || !ids)) return SCONE_EINVAL;
-    // At most n entries plus one suffix entry per f-gram of length >= 4 and
-    // one more per f-gram of length >= 6, so n * 3 bounds them.
-    if (std::ceil(3.0 * (double)n / max_load) > (double)(1ull << 40)) return SCONE_EINVAL;
-    const int slot_bytes = max_len <= kMaxLenSlot16 ? 16 : 32;
-
     hipStream_t st = static_cast<hipStream_t>(stream);
     int dev = 0;
     SCONE_HIP_TRY(hipGetDevice(&dev));
-
-    void* slots = nullptr;
-    // status word at offset 0, counts of f-grams of length >= 4 and >= 6 at 8,
-    // 16, slots in use after the build at 24
-    void* aux = nullptr;
-    int64_t* slot_of = nullptr;
-    int rc = SCONE_OK;
-    unsigned long long haux[4] = {0, 0, 0, 0};
-    unsigned hstatus = 0;
-    unsigned long long hcount[2] = {0, 0};
-    uint64_t cap = 64;
-    unsigned* status = nullptr;
-    if (hipMalloc(&aux, 32) != hipSuccess) {
+    void *ctl = nullptr, *slots = nullptr;
+    if (hipMalloc(&ctl, kControlBytes) != hipSuccess) {
         (void)hipGetLastError();
         return SCONE_ENOMEM;
     }
-    status = static_cast<unsigned*>(aux);
-    if (hipMemsetAsync(aux, 0, 32, st) != hipSuccess) {
-        rc = SCONE_EHIP;
-        goto fail;
-    }
-    if (n > 0 && max_len >= 4) {
-        unsigned long long* counts =
-            reinterpret_cast<unsigned long long*>(static_cast<uint8_t*>(aux) + 8);
-        const hipError_t e = launch_blocks((n + kBuildThreads - 1) / kBuildThreads, kBuildThreads,
-                                           [&](int64_t b0, dim3 grid) {
-            hipLaunchKernelGGL(k_count_long, grid, dim3(kBuildThreads), 0, st, lengths, n,
-                               (int)max_len, counts, b0);
-        });
-        if (e != hipSuccess ||
-            hipMemcpyAsync(hcount, counts, sizeof(hcount), hipMemcpyDeviceToHost, st) !=
-                hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess) {
-            rc = SCONE_EHIP;
-            goto fail;
-        }
-    }
-    {
-        // Slot count: smallest power of two >= max(64, entries / max_load).
-        const double entries = (double)n + (double)hcount[0] + (double)hcount[1];
-        const double want = std::max(64.0, std::ceil(entries / max_load));
-        while ((double)cap < want) cap <<= 1;
-    }
-    if (hipMalloc(&slots, cap * (uint64_t)slot_bytes) != hipSuccess ||
-        (n > 0 && hipMalloc(&slot_of, sizeof(int64_t) * (size_t)n) != hipSuccess)) {
+    uint64_t cap = 0;
+    rc = count_slots(lengths, n, max_len, max_load, static_cast<Control*>(ctl), st, cap);
+    if (rc == SCONE_OK &&
+        hipMalloc(&slots, cap * (uint64_t)slot_bytes_for(max_len)) != hipSuccess) {
         (void)hipGetLastError();
+        slots = nullptr;
         rc = SCONE_ENOMEM;
-        goto fail;
     }
-    if (hipMemsetAsync(slots, 0, cap * (uint64_t)slot_bytes, st) != hipSuccess) {
-        rc = SCONE_EHIP;
-        goto fail;
-    }
-    if (n > 0) {
-        const hipError_t e =
-            slot_bytes == 16
-                ? launch_build<16>(fgrams, lengths, ids, n, max_len, slots, cap - 1, slot_of,
-                                   status, st)
-                : launch_build<32>(fgrams, lengths, ids, n, max_len, slots, cap - 1, slot_of,
-                                   status, st);
-        if (e != hipSuccess) {
-            rc = SCONE_EHIP;
-            goto fail;
-        }
-    }
-    {
-        unsigned long long* used =
-            reinterpret_cast<unsigned long long*>(static_cast<uint8_t*>(aux) + 24);
-        const int64_t per = (int64_t)kBuildThreads * kUsedPer;
-        const hipError_t e = launch_blocks(((int64_t)cap + per - 1) / per, kBuildThreads,
-                                           [&](int64_t b0, dim3 grid) {
-            if (slot_bytes == 16)
-                hipLaunchKernelGGL(k_count_used<16>, grid, dim3(kBuildThreads), 0, st,
-                                   static_cast<const Slot16*>(slots), (int64_t)cap, used, b0);
-            else
-                hipLaunchKernelGGL(k_count_used<32>, grid, dim3(kBuildThreads), 0, st,
-                                   static_cast<const Slot32*>(slots), (int64_t)cap, used, b0);
-        });
-        if (e != hipSuccess ||
-            hipMemcpyAsync(haux, aux, sizeof(haux), hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess) {
-            rc = SCONE_EHIP;
-            goto fail;
-        }
-        hstatus = (unsigned)(haux[0] & 0xffffffffu);
-    }
-    if (hstatus) {
-        // Report argument-like data errors before structural ones.
-        const int order[] = {SCONE_ELEN, SCONE_EID, SCONE_ETOKEN, SCONE_EDUP, SCONE_EFULL};
-        rc = SCONE_EFULL;
-        for (int c : order)
-            if (hstatus & err_bit(c)) {
-                rc = c;
-                break;
-            }
-        goto fail;
-    }
-    (void)hipFree(aux);
-    if (slot_of) (void)hipFree(slot_of);
-    {
-        scone_table* t = new (std::nothrow) scone_table();
-        if (!t) {
-            (void)hipFree(slots);
-            return SCONE_ENOMEM;
-        }
-        t->device = dev;
-        t->max_len = max_len;
-        t->slot_bytes = slot_bytes;
-        t->n = n;
-        t->capacity = (int64_t)cap;
-        t->entries = (int64_t)haux[3];
-        t->slots = slots;
-        *out = t;
-    }
-    return SCONE_OK;
+    if (rc == SCONE_OK)
+        rc = fill_table(fgrams, lengths, ids, n, max_len, slots, cap, static_cast<Control*>(ctl),
+                        dev, st, out);
+    if (rc == SCONE_OK) (*out)->owned = slots;
+    else (void)hipStreamSynchronize(st);
+    if (rc != SCONE_OK && slots) (void)hipFree(slots);
+    (void)hipFree(ctl);
+    return rc;
+}
 
-fail:
-    (void)hipStreamSynchronize(st);
-    if (slots) (void)hipFree(slots);
-    if (aux) (void)hipFree(aux);
-    if (slot_of) (void)hipFree(slot_of);
+extern "C" int scone_fgram_table_bytes(const int32_t* lengths, int64_t n, int32_t max_len,
+                                       double max_load, void* scratch, void* stream,
+                                       int64_t* bytes) {
+    using namespace scone;
+    if (!bytes) return SCONE_EINVAL;
+    *bytes = 0;
+    int rc = build_sizes_ok(n, max_len, max_load);
+    if (rc != SCONE_OK) return rc;
+    if (!scratch || (uintptr_t)scratch % 256 != 0 || (n > 0 && !lengths)) return SCONE_EINVAL;
+    if (overlaps(scratch, kControlBytes, lengths, span_bytes(n, 4))) return SCONE_EINVAL;
+    uint64_t cap = 0;
+    rc = count_slots(lengths, n, max_len, max_load, static_cast<Control*>(scratch),
+                     static_cast<hipStream_t>(stream), cap);
+    if (rc == SCONE_OK) *bytes = (int64_t)(cap * (uint64_t)slot_bytes_for(max_len)) + kControlBytes;
+    return rc;
+}
+
+extern "C" int scone_build_fgram_table_in(const int32_t* fgrams, const int32_t* lengths,
+                                          const int32_t* ids, int64_t n, int32_t max_len,
+                                          double max_load, void* memory, int64_t memory_bytes,
+                                          void* stream, scone_table_t** out) {
+    using namespace scone;
+    if (!out) return SCONE_EINVAL;
+    *out = nullptr;
+    int rc = build_sizes_ok(n, max_len, max_load);
+    if (rc != SCONE_OK) return rc;
+    if (n > 0 && (!fgrams || !lengths || !ids)) return SCONE_EINVAL;
+    if (!memory || (uintptr_t)memory % 256 != 0 || memory_bytes < kControlBytes)
+        return SCONE_EINVAL;
+    if (overlaps(memory, memory_bytes, fgrams, span_bytes(n, 4 * (int64_t)max_len)) ||
+        overlaps(memory, memory_bytes, lengths, span_bytes(n, 4)) ||
+        overlaps(memory, memory_bytes, ids, span_bytes(n, 4)))
+        return SCONE_EINVAL;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    int dev = 0;
+    SCONE_HIP_TRY(hipGetDevice(&dev));
+    Control* ctl = static_cast<Control*>(memory);
+    uint64_t cap = 0;
+    rc = count_slots(lengths, n, max_len, max_load, ctl, st, cap);
+    if (rc != SCONE_OK) return rc;
+    if ((uint64_t)memory_bytes < cap * (uint64_t)slot_bytes_for(max_len) + kControlBytes)
+        return SCONE_EINVAL;
+    rc = fill_table(fgrams, lengths, ids, n, max_len,
+                    static_cast<uint8_t*>(memory) + kControlBytes, cap, ctl, dev, st, out);
+    if (rc != SCONE_OK) (void)hipStreamSynchronize(st);
     return rc;
 }

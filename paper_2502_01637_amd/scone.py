@@ -40,6 +40,12 @@ def _declare(L):
     L.scone_build_fgram_table.argtypes = [P, P, P, I64, I32, ctypes.c_double, P,
                                           ctypes.POINTER(P)]
     L.scone_build_fgram_table.restype = I
+    L.scone_build_fgram_table_in.argtypes = [P, P, P, I64, I32, ctypes.c_double, P, I64, P,
+                                             ctypes.POINTER(P)]
+    L.scone_build_fgram_table_in.restype = I
+    L.scone_fgram_table_bytes.argtypes = [P, I64, I32, ctypes.c_double, P, P,
+                                          ctypes.POINTER(I64)]
+    L.scone_fgram_table_bytes.restype = I
     L.scone_lookup.argtypes = [P, P, I64, I64, I32, P, P, P]
     L.scone_lookup.restype = I
     L.scone_lookup_counted.argtypes = [P, P, I64, I64, I32, P, P, P, P]
@@ -150,10 +156,13 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 class Table:
-    """A built f-gram dictionary (owns the library's table handle)."""
+    """A built f-gram dictionary (owns the library's table handle and, when the
+    slots come from torch's caching allocator, their memory)."""
 
-    def __init__(self, handle: ctypes.c_void_p, device: torch.device):
+    def __init__(self, handle: ctypes.c_void_p, device: torch.device,
+                 memory: Optional[torch.Tensor] = None):
         self._h = handle
+        self._memory = memory
         self.device = device
         n, cap, ent = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int64()
         ml, sb = ctypes.c_int32(), ctypes.c_int32()
@@ -177,6 +186,11 @@ class Table:
         if self._h is not None:
             lib().scone_table_destroy(self._h)
             self._h = None
+            if self._memory is not None:
+                # lookups on any stream may still read the slots: wait, as
+                # freeing device memory does, before the allocator has them back
+                memory, self._memory = self._memory, None
+                torch.cuda.synchronize(memory.device)
 
     def __del__(self):
         try:
@@ -194,12 +208,23 @@ def build_fgram_table(fgrams: torch.Tensor, lengths: torch.Tensor, ids: torch.Te
     n, K = fgrams.shape
     if lengths.numel() != n or ids.numel() != n:
         raise ValueError("fgrams, lengths and ids disagree on n")
-    h = ctypes.c_void_p()
+    h, need, memory = ctypes.c_void_p(), ctypes.c_int64(), None
     with torch.cuda.device(fgrams.device):
-        rc = lib().scone_build_fgram_table(_ptr(fgrams), _ptr(lengths), _ptr(ids), n, K,
-                                           float(max_load), _stream(stream), ctypes.byref(h))
+        st = _stream(stream)
+        scratch = _scratch(256, fgrams.device, stream)
+        if scratch is not None and lib().scone_fgram_table_bytes(
+                _ptr(lengths), n, K, float(max_load), scratch.data_ptr(), st,
+                ctypes.byref(need)) == OK:
+            memory = _scratch(need.value, fgrams.device, stream)
+        if memory is not None:
+            rc = lib().scone_build_fgram_table_in(
+                _ptr(fgrams), _ptr(lengths), _ptr(ids), n, K, float(max_load),
+                memory.data_ptr(), memory.numel(), st, ctypes.byref(h))
+        else:  # arguments that the library refuses, or no memory left for torch
+            rc = lib().scone_build_fgram_table(_ptr(fgrams), _ptr(lengths), _ptr(ids), n, K,
+                                               float(max_load), st, ctypes.byref(h))
     _check(rc, "scone_build_fgram_table")
-    return Table(h, fgrams.device)
+    return Table(h, fgrams.device, memory)
 
 
 def lookup(table: Table, token_ids: torch.Tensor, max_n: int,

@@ -1,0 +1,119 @@
+"""The dictionary's build where its concurrent passes can go wrong: keys that
+share their first words, suffixes that many f-grams share, duplicates, and the
+build in the caller's memory."""
+import ctypes
+import itertools
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2502_01637_amd as S
+from gpu_util import build_gpu, dev
+
+
+def all_ngrams(alphabet, K, keep, rng):
+    rows = [g for n in range(2, K + 1) for g in itertools.product(alphabet, repeat=n)]
+    rows = [rows[i] for i in rng.permutation(len(rows))[:int(keep * len(rows))]]
+    fg = np.full((len(rows), K), -1, dtype=np.int32)
+    for i, r in enumerate(rows):
+        fg[i, :len(r)] = r
+    return fg, np.array([len(r) for r in rows], dtype=np.int32)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("load", [0.25, 0.9])
+@pytest.mark.parametrize("K", [2, 3, 4, 5, 6, 7])
+def test_dense_sets_with_shared_suffixes(K, load):
+    """Every third n-gram is left out, so many suffixes are markers; the tokens
+    differ in their lowest or highest bits only, so keys share whole words."""
+    rng = np.random.default_rng(K)
+    alphabet = [0, 1, 65535] if K >= 6 else [0, 1, 4096, 61440, 65535]
+    fg, ln = all_ngrams(alphabet, K, 0.67, rng)
+    ids = (70000 + rng.permutation(len(ln))).astype(np.int32)
+    o = oracle.OracleTable(fg, ln, ids)
+    X = rng.choice(alphabet, size=(6, 700)).astype(np.int32)
+    for _ in range(2):
+        t = build_gpu(fg, ln, ids, max_load=load)
+        suffixes = {tuple(g[n - 3:n]) for g, n in zip(fg.tolist(), ln) if n >= 4}
+        suffixes |= {tuple(g[n - 5:n]) for g, n in zip(fg.tolist(), ln) if n >= 6}
+        have = {tuple(g[:n]) for g, n in zip(fg.tolist(), ln)}
+        # every suffix has an entry; a marker may be there twice
+        assert len(have) + len(suffixes - have) <= t.entries
+        assert t.entries <= len(have) + 2 * len(suffixes - have)
+        for max_n in {2, 3, K}:
+            got, ml = S.lookup(t, dev(X), max_n, want_len=True)
+            want, wl = o.lookup(X, max_n)
+            assert np.array_equal(got.cpu().numpy(), want)
+            assert np.array_equal(ml.cpu().numpy(), wl)
+        t.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K", [3, 5, 7])
+def test_one_duplicate_is_found(K):
+    rng = np.random.default_rng(K)
+    fg, ln = all_ngrams([0, 1, 65535], K, 0.9, rng)
+    ids = np.arange(len(ln), dtype=np.int32)
+    build_gpu(fg, ln, ids).close()
+    for n in range(2, K + 1):
+        i = int(np.nonzero(ln == n)[0][0])
+        with pytest.raises(S.SconeError) as e:
+            build_gpu(np.concatenate([fg, fg[i:i + 1]]), np.append(ln, ln[i]),
+                      np.append(ids, 5).astype(np.int32))
+        assert e.value.code == S.scone.EDUP
+
+
+@pytest.mark.gpu
+def test_hot_suffix_and_callers_memory():
+    """200,000 f-grams that end alike; built in the caller's memory, where a
+    short, misaligned or overlapping block is refused."""
+    n, K = 200_000, 7
+    rng = np.random.default_rng(1)
+    fg = np.full((n, K), 7, dtype=np.int32)
+    fg[:, 0], fg[:, 1] = np.arange(n) % 500, np.arange(n) // 500
+    ln = np.full(n, K, dtype=np.int32)
+    ids = np.arange(n, dtype=np.int32)
+    t = [dev(fg), dev(ln), dev(ids)]
+    L, st = S.scone.lib(), torch.cuda.current_stream().cuda_stream
+    scratch = torch.empty(256, dtype=torch.uint8, device="cuda")
+    need = ctypes.c_int64()
+    assert L.scone_fgram_table_bytes(t[1].data_ptr(), n, K, 0.25, scratch.data_ptr(), st,
+                                     ctypes.byref(need)) == S.scone.OK
+    # 3 n entries at most at load 0.25: 2^22 slots of 32 bytes
+    assert need.value == (1 << 22) * 32 + 256
+    mem = torch.empty(need.value + 256, dtype=torch.uint8, device="cuda")
+
+    def build(ptr, nbytes):
+        h = ctypes.c_void_p()
+        rc = L.scone_build_fgram_table_in(t[0].data_ptr(), t[1].data_ptr(), t[2].data_ptr(), n,
+                                          K, 0.25, ptr, nbytes, st, ctypes.byref(h))
+        return rc, h
+
+    for ptr, nbytes in [(mem.data_ptr(), need.value - 1), (mem.data_ptr() + 16, need.value),
+                        (t[0].data_ptr(), need.value), (None, need.value)]:
+        rc, h = build(ptr, nbytes)
+        assert rc == S.scone.EINVAL and not h.value
+    rc, h = build(mem.data_ptr(), need.value)
+    assert rc == S.scone.OK
+    table = S.Table(h, mem.device, mem)
+    assert n + 2 <= table.entries <= n + 4
+    X = dev(fg[rng.integers(0, n, 300)])
+    got, ml = S.lookup(table, X, K, want_len=True)
+    assert np.array_equal(got.cpu().numpy()[:, -1],
+                          X.cpu().numpy()[:, 0] + 500 * X.cpu().numpy()[:, 1])
+    assert (ml.cpu().numpy()[:, -1] == K).all()
+    table.close()
+
+
+def test_size_arguments():
+    L = S.scone.lib()
+    b = ctypes.c_int64(5)
+    for n, K, load in [(-1, 3, 0.5), (1, 8, 0.5), (1, 3, 0.0), (1, 3, 0.95)]:
+        assert L.scone_fgram_table_bytes(None, n, K, load, None, None,
+                                         ctypes.byref(b)) == S.scone.EINVAL
+        assert b.value == 0
+    assert L.scone_fgram_table_bytes(None, 0, 3, 0.5, None, None, None) == S.scone.EINVAL
+    assert L.scone_fgram_table_bytes(None, 0, 3, 0.5, None, None,
+                                     ctypes.byref(b)) == S.scone.EINVAL
