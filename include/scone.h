@@ -190,8 +190,8 @@ int scone_tag(const scone_table_t* table, const int32_t* token_ids, int64_t B, i
  *  rows       [n_rows, row_bytes] table: device memory (placement
  *             SCONE_PLACE_HBM) or host-mapped pinned memory
  *             (SCONE_PLACE_HOST).
- *  row_bytes  > 0.  Rows move in 16-byte vectors when row_bytes and both
- *             pointers allow it, otherwise in the widest unit that does.
+ *  row_bytes  > 0, any width and alignment.  Rows of 16 bytes and more move
+ *             in 16-byte vectors.
  *  out        [n_tok, row_bytes] device output; sharing memory with `rows`
  *             or with fgram_ids gives SCONE_EINVAL.
  *
@@ -244,9 +244,9 @@ int scone_embed(const scone_table_t* table, const int32_t* token_ids, int64_t B,
  * Returns SCONE_EINVAL when any output (next_ids, next_len, out) shares
  * memory with an input (next_tokens, cur_ids) or with another output: the
  * launch writes them while its other workgroups read; otherwise errors as
- * for scone_lookup and scone_gather.  Rows of 1, 2, 4 or 8 KiB, 16-byte aligned,
- * take the one-launch kernel; other widths run the lookup and gather kernels
- * back to back with the same results.  Asynchronous on `stream`.
+ * for scone_lookup and scone_gather.  Rows of 16 bytes and more take one launch;
+ * narrower ones run the lookup and gather kernels back to back with the same
+ * results.  Asynchronous on `stream`.
  */
 int scone_embed_pipelined(const scone_table_t* table, const int32_t* next_tokens, int64_t B,
                           int64_t T, int32_t max_n, int32_t* next_ids, int8_t* next_len,

@@ -11,50 +11,108 @@
 // separate kernels back to back: the hash probes are random HBM reads that
 // cost bandwidth the row stream would otherwise use, so overlapping them
 // hides their latency but not their cost.
+#include "row_copy.h"
 #include "tile_lookup.h"
 
 namespace scone {
 namespace {
 
+// How a tile's rows are cut into units: 16-byte units of rows of 2^shift of them,
+// 16-byte aligned; 16-byte units of rows of any width and alignment (RowUnits);
+// the same with 64-bit indexes, for rows of 2 GiB and more; or single bytes, for
+// rows below 16.
+enum RowMode { kRowPow2 = 0, kRowAny = 1, kRowWide = 2, kRowBytes = 3 };
+
+template <RowMode kMode>
+struct Unit {
+    typedef u32x4_any type;
+    typedef uint32_t index;
+};
+template <>
+struct Unit<kRowPow2> {
+    typedef u32x4 type;
+    typedef uint32_t index;
+};
+template <>
+struct Unit<kRowWide> {
+    typedef u32x4_any type;
+    typedef uint64_t index;
+};
+template <>
+struct Unit<kRowBytes> {
+    typedef uint8_t type;
+    typedef uint32_t index;
+};
+
 // Row copy helpers for one batch of U units per thread (unit i of the tile's
 // output block).  A bad id reads row 0 and the unit is zeroed afterwards, so
 // the loads of a batch carry no branch and stay in flight together.
-template <typename V, int U, bool kPow2>
+template <RowMode kMode, int U>
 struct TileCopy {
+    typedef typename Unit<kMode>::type V;
+    typedef typename Unit<kMode>::index I;
     const int32_t* s_id;
-    const V* __restrict__ rows;
-    V* __restrict__ dst;
-    int64_t n_rows, upr;
-    int shift;
+    const uint8_t* __restrict__ rows;
+    uint8_t* __restrict__ dst;
+    int64_t n_rows;
+    const RowUnits& ru;
 
-    __device__ __forceinline__ void load(int64_t base, V (&v)[U], bool (&ok)[U]) const {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t i = base + (int64_t)u * kTileThreads;
-            const int64_t r = kPow2 ? (i >> shift) : (i / upr);
-            const int64_t c = i - r * upr;
-            const int64_t id = s_id[r];
-            ok[u] = (id >= 0) & (id < n_rows);
-            const int64_t src = ok[u] ? id : 0;
-            v[u] = rows[(kPow2 ? (src << shift) : src * upr) + c];
+    __device__ __forceinline__ I per_row() const {
+        return kMode == kRowWide ? (I)((ru.row_bytes + 15) / 16) : (I)ru.upr;
+    }
+    __device__ __forceinline__ void split(I i, I& r, int64_t& off) const {
+        if constexpr (kMode == kRowPow2) {
+            r = i >> ru.log;
+            off = (int64_t)(i & (ru.upr - 1)) * 16;
+        } else if constexpr (kMode == kRowBytes) {
+            r = ru.div(i);
+            off = (int64_t)(i - r * ru.upr);
+        } else {
+            r = kMode == kRowWide ? i / per_row() : (I)ru.div((uint32_t)i);
+            off = ru.offset(i - r * per_row());
         }
     }
-    __device__ __forceinline__ bool store(int64_t base, V (&v)[U], const bool (&ok)[U]) const {
+    __device__ __forceinline__ V load_one(I i, bool& ok) const {
+        I r;
+        int64_t off;
+        split(i, r, off);
+        const int64_t id = s_id[r];
+        ok = (id >= 0) & (id < n_rows);
+        const int64_t src = ok ? id : 0;
+        const int64_t at = kMode == kRowPow2 ? src << (ru.log + 4) : src * ru.row_bytes;
+        return *reinterpret_cast<const V*>(rows + at + off);
+    }
+    __device__ __forceinline__ void store_one(I i, V v, bool ok) const {
+        int64_t at;
+        if constexpr (kMode == kRowAny || kMode == kRowWide) {
+            I r;
+            split(i, r, at);
+            at += (int64_t)r * ru.row_bytes;
+        } else {
+            at = (int64_t)i * sizeof(V);
+        }
+        __builtin_nontemporal_store(ok ? v : V{}, reinterpret_cast<V*>(dst + at));
+    }
+    __device__ __forceinline__ void load(I base, V (&v)[U], bool (&ok)[U]) const {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = load_one(base + u * kTileThreads, ok[u]);
+    }
+    __device__ __forceinline__ bool store(I base, V (&v)[U], const bool (&ok)[U]) const {
         bool bad = false;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            __builtin_nontemporal_store(ok[u] ? v[u] : V{}, dst + base + (int64_t)u * kTileThreads);
+            store_one(base + u * kTileThreads, v[u], ok[u]);
             bad |= !ok[u];
         }
         return bad;
     }
 };
 
-template <int SB, int G, typename V, int U, bool kPow2>
+template <int SB, int G, RowMode kMode, int U>
 __global__ __launch_bounds__(kTileThreads) void k_embed(
     const typename SlotOps<SB>::Slot* __restrict__ slots, uint64_t mask,
     const int32_t* __restrict__ X, int64_t T, int P, int max_n, int64_t tiles_per_row,
-    const V* __restrict__ rows, int64_t n_rows, int64_t upr, int shift, V* __restrict__ out,
+    const uint8_t* __restrict__ rows, int64_t n_rows, RowUnits ru, uint8_t* __restrict__ out,
     int32_t* __restrict__ ids_out, int8_t* __restrict__ len_out, unsigned* __restrict__ err,
     int64_t block0) {
     __shared__ int32_t s_tok[TileShape<G>::kPositions + kMaxHalo];
@@ -86,13 +144,15 @@ __global__ __launch_bounds__(kTileThreads) void k_embed(
     // Copy the tile's rows: positions t0 .. t0+npos-1 own one contiguous
     // output block of npos * upr units.  Whole batches are software-pipelined
     // (the next batch's loads are issued before this batch's stores).
-    const int64_t npos = (T - t0) < P ? (T - t0) : P;
-    const int64_t total = npos * upr;
-    const TileCopy<V, U, kPow2> cp{s_id, rows, out + (b * T + t0) * upr, n_rows, upr, shift};
-    constexpr int64_t kStride = (int64_t)kTileThreads * U;
-    const int64_t whole = total / kStride * kStride;
+    const uint32_t npos = (uint32_t)((T - t0) < P ? (T - t0) : P);
+    const TileCopy<kMode, U> cp{s_id, rows, out + (b * T + t0) * ru.row_bytes, n_rows, ru};
+    typedef typename Unit<kMode>::type V;
+    typedef typename Unit<kMode>::index I;
+    const I total = npos * cp.per_row();
+    constexpr I kStride = kTileThreads * U;
+    const I whole = total / kStride * kStride;
     bool bad = false;
-    int64_t base = threadIdx.x;
+    I base = threadIdx.x;
     if (whole > 0) {
         V a[U];
         bool oka[U];
@@ -111,58 +171,53 @@ __global__ __launch_bounds__(kTileThreads) void k_embed(
         bad |= cp.store(base, a, oka);
         base += kStride;
     }
-    for (int64_t i = base; i < total; i += kTileThreads) {  // ragged remainder
-        const int64_t r = kPow2 ? (i >> shift) : (i / upr);
-        const int64_t c = i - r * upr;
-        const int64_t id = s_id[r];
-        const bool okk = (id >= 0) & (id < n_rows);
-        __builtin_nontemporal_store(okk ? rows[id * upr + c] : V{}, cp.dst + i);
+    for (I i = base; i < total; i += kTileThreads) {  // ragged remainder
+        bool okk;
+        const V v = cp.load_one(i, okk);
+        cp.store_one(i, v, okk);
         bad |= !okk;
     }
     if (bad) atomicOr(err, err_bit(SCONE_EROW));
 }
 
-template <int SB, int G, typename V, bool kPow2>
-hipError_t launch(const scone_table* tb, const int32_t* X, int64_t B, int64_t T, int max_n,
-                  const void* rows, int64_t n_rows, int64_t upr, int shift, void* out,
-                  int32_t* ids, int8_t* lens, unsigned* err, hipStream_t st) {
+struct Call {
+    const scone_table* tb;
+    const int32_t* X;
+    int64_t B, T;
+    int max_n;
+    const void* rows;
+    int64_t n_rows, row_bytes;
+    void* out;
+    int32_t* ids;
+    int8_t* lens;
+    unsigned* err;
+    hipStream_t st;
+};
+
+template <int SB, int G, RowMode kMode>
+hipError_t launch(const Call& c, RowUnits ru) {
     using Slot = typename SlotOps<SB>::Slot;
     // Positions per workgroup: up to 16 positions and 32 KiB of rows, at
     // least 4 positions.  Short-lived workgroups let the probes of some
     // overlap the copies of others on the same compute unit (16 to 32 KiB
     // per workgroup measured best for 2 and 4 KiB rows).
-    const int64_t row_bytes = upr * (int64_t)sizeof(V);
     int P = TileShape<G>::kPositions < 16 ? TileShape<G>::kPositions : 16;
-    while (P > 4 && (int64_t)P * row_bytes > (32 << 10)) P >>= 1;
-    const int64_t tiles = (T + P - 1) / P;
-    return launch_blocks(B * tiles, kTileThreads, [&](int64_t b0, dim3 grid) {
-        hipLaunchKernelGGL((k_embed<SB, G, V, 4, kPow2>), grid, dim3(kTileThreads), 0, st,
-                           static_cast<const Slot*>(tb->slots), (uint64_t)tb->capacity - 1, X,
-                           T, P, max_n, tiles, static_cast<const V*>(rows), n_rows, upr, shift,
-                           static_cast<V*>(out), ids, lens, err, b0);
+    while (P > 4 && (int64_t)P * c.row_bytes > (32 << 10)) P >>= 1;
+    const int64_t tiles = (c.T + P - 1) / P;
+    return launch_blocks(c.B * tiles, kTileThreads, [&](int64_t b0, dim3 grid) {
+        hipLaunchKernelGGL((k_embed<SB, G, kMode, 4>), grid, dim3(kTileThreads), 0, c.st,
+                           static_cast<const Slot*>(c.tb->slots), (uint64_t)c.tb->capacity - 1,
+                           c.X, c.T, P, c.max_n, tiles, static_cast<const uint8_t*>(c.rows),
+                           c.n_rows, ru, static_cast<uint8_t*>(c.out), c.ids, c.lens, c.err, b0);
     });
 }
 
-template <int SB, typename V, bool kPow2>
-hipError_t dispatch(const scone_table* tb, const int32_t* X, int64_t B, int64_t T, int max_n,
-                    const void* rows, int64_t n_rows, int64_t upr, int shift, void* out,
-                    int32_t* ids, int8_t* lens, unsigned* err, hipStream_t st) {
-    if (tile_lanes_for(max_n) == 1)
-        return launch<SB, 1, V, kPow2>(tb, X, B, T, max_n, rows, n_rows, upr, shift, out, ids,
-                                       lens, err, st);
-    return launch<SB, 2, V, kPow2>(tb, X, B, T, max_n, rows, n_rows, upr, shift, out, ids, lens,
-                                   err, st);
-}
-
-template <typename V, bool kPow2>
-hipError_t dispatch_slots(const scone_table* tb, const int32_t* X, int64_t B, int64_t T,
-                          int max_n, const void* rows, int64_t n_rows, int64_t upr, int shift,
-                          void* out, int32_t* ids, int8_t* lens, unsigned* err, hipStream_t st) {
-    return tb->slot_bytes == 16
-               ? dispatch<16, V, kPow2>(tb, X, B, T, max_n, rows, n_rows, upr, shift, out, ids,
-                                        lens, err, st)
-               : dispatch<32, V, kPow2>(tb, X, B, T, max_n, rows, n_rows, upr, shift, out, ids,
-                                        lens, err, st);
+template <RowMode kMode>
+hipError_t dispatch(const Call& c, const RowUnits& ru) {
+    const bool one = tile_lanes_for(c.max_n) == 1;
+    if (c.tb->slot_bytes == 16)
+        return one ? launch<16, 1, kMode>(c, ru) : launch<16, 2, kMode>(c, ru);
+    return one ? launch<32, 1, kMode>(c, ru) : launch<32, 2, kMode>(c, ru);
 }
 
 }  // namespace
@@ -207,17 +262,16 @@ extern "C" int scone_embed(const scone_table_t* table, const int32_t* token_ids,
         if (e0 == hipSuccess) e0 = launch_zero_rows(out, B * T * row_bytes, err, st);
         return status_of(e0);
     }
-    const uintptr_t align = (uintptr_t)rows | (uintptr_t)out | (uintptr_t)row_bytes;
-    hipError_t e;
-    if ((align & 15) == 0 && ((row_bytes / 16) & (row_bytes / 16 - 1)) == 0) {
-        const int64_t upr = row_bytes / 16;
-        int shift = 0;
-        while (((int64_t)1 << shift) < upr) ++shift;
-        e = dispatch_slots<u32x4, true>(table, token_ids, B, T, eff, rows, n_rows, upr, shift,
-                                        out, fgram_ids, match_len, err, st);
-    } else {
-        e = dispatch_slots<uint8_t, false>(table, token_ids, B, T, eff, rows, n_rows, row_bytes,
-                                           0, out, fgram_ids, match_len, err, st);
+    const Call c{table, token_ids, B, T, eff, rows, n_rows, row_bytes, out, fgram_ids, match_len,
+                 err, st};
+    if (row_bytes < 16) return status_of(dispatch<kRowBytes>(c, row_units(row_bytes, 1)));
+    if (!unit_row_bytes(row_bytes)) {
+        RowUnits wide{};
+        wide.row_bytes = row_bytes;
+        return status_of(dispatch<kRowWide>(c, wide));
     }
-    return status_of(e);
+    const RowUnits ru = row_units(row_bytes);
+    const uintptr_t align = (uintptr_t)rows | (uintptr_t)out | (uintptr_t)row_bytes;
+    const bool pow2 = (align & 15) == 0 && (ru.upr & (ru.upr - 1)) == 0;
+    return status_of(pow2 ? dispatch<kRowPow2>(c, ru) : dispatch<kRowAny>(c, ru));
 }

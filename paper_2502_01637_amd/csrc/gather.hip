@@ -3,10 +3,11 @@
 // The embedding fetch is a pure memory copy (Section 1), so the kernel is an
 // HBM-bound streaming copy whose source rows are chosen by the ids.  Rows of
 // 1 or 2 KiB (16-byte aligned) take one wavefront per row, rows of 4 or 8 KiB
-// one wavefront per KiB (gather_row_waves).  Any other
-// width views the output as a flat array of V-sized units (16 bytes when the
-// row width and the pointers allow).  Consecutive lanes own consecutive units, so
-// one wavefront reads 64 * 16 B = 1 KiB of one row per instruction and writes
+// one wavefront per KiB (gather_row_waves).  Any other width from 16 bytes up
+// is a flat array of 16-byte units (copy_units), whatever its alignment;
+// narrower rows are a flat array of V-sized units, V as wide as the row width
+// and the pointers allow.  Consecutive lanes own consecutive units, so
+// one wavefront reads 64 * 16 B = 1 KiB of a row per instruction and writes
 // the same 1 KiB of the output; each thread issues all of its U loads before
 // its U stores to keep enough bytes in flight.  Output stores are
 // non-temporal: the output is not re-read by this path, and keeping it out of
@@ -88,6 +89,13 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather_rows(
     copy_row_part<U, W>(ids, r, (int)(w - r * W), rows, n_rows, out, err);
 }
 
+template <int U>
+__global__ __launch_bounds__(kGatherThreads) void k_gather_units(
+    const int32_t* __restrict__ ids, int64_t n_tok, RowUnits ru, const uint8_t* __restrict__ rows,
+    int64_t n_rows, uint8_t* __restrict__ out, unsigned* __restrict__ err, int64_t block0) {
+    copy_units<U>(ids, n_tok, block_index(block0), ru, rows, n_rows, out, err);
+}
+
 // Every id is out of range when the table has no rows: zero the output.
 template <typename V>
 __global__ __launch_bounds__(kGatherThreads) void k_zero(int64_t total, V* __restrict__ out,
@@ -156,7 +164,15 @@ hipError_t launch_gather_any(const int32_t* ids, int64_t n_tok, const void* rows
             }
         });
     }
-    if ((align & 15) == 0)
+    if (unit_row_bytes(row_bytes) && n_rows > 0) {
+        const RowUnits ru = row_units(row_bytes);
+        return launch_blocks(unit_blocks(n_tok, ru), kGatherThreads, [&](int64_t b0, dim3 grid) {
+            hipLaunchKernelGGL(k_gather_units<kUnitsPerThread>, grid, dim3(kGatherThreads), 0, st,
+                               ids, n_tok, ru, static_cast<const uint8_t*>(rows), n_rows,
+                               static_cast<uint8_t*>(out), err, b0);
+        });
+    }
+    if ((align & 15) == 0)  // no rows, or rows of 2 GiB and more
         return launch_gather<u32x4, 4>(ids, n_tok, rows, n_rows, row_bytes, out, err, st);
     if ((align & 7) == 0)
         return launch_gather<u32x2, 4>(ids, n_tok, rows, n_rows, row_bytes, out, err, st);

@@ -40,6 +40,25 @@ __global__ __launch_bounds__(kTileThreads) void k_pipelined(
     copy_row_part<U, W>(cur_ids, r, (int)(w - r * W), rows, n_rows, out, err);
 }
 
+// The same for rows of any other width from 16 bytes up (copy_units).
+template <int SB, int G>
+__global__ __launch_bounds__(kTileThreads) void k_pipelined_units(
+    const typename SlotOps<SB>::Slot* __restrict__ slots, uint64_t mask,
+    const int32_t* __restrict__ X, int64_t T, int max_n, int64_t tiles_per_row,
+    int64_t n_lookup_blocks, int32_t* __restrict__ next_ids, int8_t* __restrict__ next_len,
+    const int32_t* __restrict__ cur_ids, int64_t n_cur, RowUnits ru,
+    const uint8_t* __restrict__ rows, int64_t n_rows, uint8_t* __restrict__ out,
+    unsigned* __restrict__ err, int64_t block0) {
+    __shared__ int32_t s_tok[TileShape<G>::kPositions + kMaxHalo];
+    const int64_t blk = block_index(block0);
+    if (blk < n_lookup_blocks) {  // workgroup-uniform
+        lookup_block<SB, G>(slots, mask, X, T, max_n, tiles_per_row, blk, s_tok, next_ids,
+                            next_len, err);
+        return;
+    }
+    copy_units<kUnitsPerThread>(cur_ids, n_cur, blk - n_lookup_blocks, ru, rows, n_rows, out, err);
+}
+
 struct Step {
     const scone_table* tb;
     const int32_t* X;
@@ -50,11 +69,28 @@ struct Step {
     const int32_t* cur_ids;
     int64_t n_cur;
     const void* rows;
-    int64_t n_rows;
+    int64_t n_rows, row_bytes;
     void* out;
     unsigned* err;
     hipStream_t st;
 };
+
+template <int SB, int G>
+hipError_t launch_units(const Step& s) {
+    using Slot = typename SlotOps<SB>::Slot;
+    constexpr int P = TileShape<G>::kPositions;
+    const int64_t tiles = (s.T + P - 1) / P;
+    const int64_t n_lookup = s.B * tiles;
+    const RowUnits ru = row_units(s.row_bytes);
+    return launch_blocks(n_lookup + unit_blocks(s.n_cur, ru), kTileThreads,
+                         [&](int64_t b0, dim3 grid) {
+        hipLaunchKernelGGL((k_pipelined_units<SB, G>), grid, dim3(kTileThreads), 0, s.st,
+                           static_cast<const Slot*>(s.tb->slots), (uint64_t)s.tb->capacity - 1,
+                           s.X, s.T, s.max_n, tiles, n_lookup, s.next_ids, s.next_len,
+                           s.cur_ids, s.n_cur, ru, static_cast<const uint8_t*>(s.rows), s.n_rows,
+                           static_cast<uint8_t*>(s.out), s.err, b0);
+    });
+}
 
 template <int SB, int G, int U>
 hipError_t launch(const Step& s) {
@@ -76,6 +112,7 @@ hipError_t launch(const Step& s) {
 template <int SB, int G>
 hipError_t by_units(const Step& s, int units) {
     switch (units) {
+        case 0: return launch_units<SB, G>(s);
         case 1: return launch<SB, G, 1>(s);
         case 2: return launch<SB, G, 2>(s);
         case 4: return launch<SB, G, 4>(s);
@@ -130,16 +167,16 @@ extern "C" int scone_embed_pipelined(const scone_table_t* table, const int32_t* 
     if (!err) return SCONE_EHIP;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int eff = max_n < table->max_len ? max_n : table->max_len;
-    const int units = wave_row_units(row_bytes);
     const bool aligned = (((uintptr_t)rows | (uintptr_t)out) & 15) == 0;
+    const int units = aligned ? wave_row_units(row_bytes) : 0;
     hipError_t e = hipSuccess;
-    if (n_next > 0 && n_cur > 0 && units > 0 && aligned && n_rows > 0) {
+    if (n_next > 0 && n_cur > 0 && unit_row_bytes(row_bytes) && n_rows > 0) {
         const Step s{table, next_tokens, B, T, eff, next_ids, next_len, cur_ids, n_cur,
-                     rows, n_rows, out, err, st};
+                     rows, n_rows, row_bytes, out, err, st};
         e = table->slot_bytes == 16 ? by_lanes<16>(s, units) : by_lanes<32>(s, units);
     } else {
-        // One half empty, or rows the one-wavefront copy does not cover: the
-        // two kernels of scone_lookup and scone_gather, back to back.
+        // One half empty, or rows below 16 bytes: the two kernels of
+        // scone_lookup and scone_gather, back to back.
         if (n_next > 0)
             e = launch_lookup(table, next_tokens, B, T, eff, next_ids, next_len, err, st);
         if (e == hipSuccess && n_cur > 0)
