@@ -1,17 +1,35 @@
 // F-gram discovery on the device: Algorithm 3 with the K-1 linear scans of
 // Section 3.1.
 //
-// Scan n counts the n-grams of every sequence in an open-addressing table
-// keyed by an exact 64-bit code.  For n = 2 the code is (t0 << 16) | t1.
-// From n = 3 on, an n-gram is counted only when both its (n-1)-prefix and its
-// (n-1)-suffix survived scan n-1 (count >= the minimum count): an n-gram that
-// reaches the minimum appears inside both of them at least as often, so
-// nothing that could survive is skipped.  Every survivor of scan n-1 has a
-// dense id, and an n-gram is coded as (dense id of its prefix << 16) | last
-// token, which is exact and fits 64 bits at any length, so the counting
-// tables need only a 64-bit compare-and-swap.  After each scan the survivors
-// get dense ids and every position learns the id of the survivor ending there
-// (or -1), which is all the next scan reads.
+// Scan n counts the n-grams of every sequence by an exact 64-bit code.  For
+// n = 2 the code is (t0 << 16) | t1.  From n = 3 on, an n-gram is counted only
+// when both its (n-1)-prefix and its (n-1)-suffix survived scan n-1 (count >=
+// the minimum count): an n-gram that reaches the minimum appears inside both
+// of them at least as often, so nothing that could survive is skipped.  Every
+// survivor of scan n-1 has a dense id, and an n-gram is coded as (dense id of
+// its prefix << 16) | last token, which is exact and fits 47 bits at any
+// length.  After each scan the survivors get dense ids and every position
+// learns the id of the survivor ending there (or -1), which is all the next
+// scan reads.
+//
+// A scan counts without a global counting table.  A random read or atomic
+// update reaches about 20 G/s on this card whatever it carries, and a table
+// for every distinct n-gram took 28M of them per scan of 16.8M tokens, 75 us to
+// clear and 480 us to read back.  Instead the codes are partitioned by hash
+// into buckets that a workgroup counts in LDS:
+//
+//   k_offsets    where each bucket's items start, from the sizes that the
+//                previous pass over the positions counted (an upper bound)
+//   k_partition  a workgroup merges equal codes of its chunk in LDS and writes
+//                one 8-byte item (code, count) per distinct code to its bucket
+//   k_bucket     one workgroup per bucket: counts in LDS, then the survivors'
+//                dense ids and the candidates, in runs
+//   k_surv_*     a hash table of the survivors alone (code -> dense id)
+//   k_ids        every position looks its code up there and counts the next
+//                scan's bucket sizes on the way
+//
+// 16.8M tokens (K = 5, 1M f-grams kept): scans 2 to 5 took 2,280, 1,760, 1,040
+// and 750 us with the global table.
 //
 // The candidates are all 2-grams and the survivors of scans 3..K; the top S by
 // count are found with a threshold search (equal counts at the threshold are
@@ -25,212 +43,452 @@ namespace scone {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kWide = 1024;  // threads of the passes that count in LDS
 constexpr uint64_t kEmptyKey = ~0ull;
 
-struct alignas(16) CountSlot {
+// An item: code << 14 | count, the count at most a chunk's 8,192 positions.
+constexpr int kCountBits = 14;
+constexpr uint64_t kCountMask = (1u << kCountBits) - 1;
+constexpr int kMaxChunk = 8192;
+// Buckets, at most; one per 4,096 positions up to there.  Each has a region per
+// group of chunks (chunk index mod 8): consecutive workgroups run on different
+// XCDs, so the runs of a few items that chunks append to a region come through
+// one L2, which joins them into whole lines.
+constexpr int kMaxBuckets = 1024;
+constexpr int kGroups = 8;
+
+struct alignas(16) SurvSlot {
     uint64_t key;
-    uint32_t count;
     int32_t dense;
+    int32_t pad;
 };
 
 __device__ __forceinline__ uint64_t count_hash(uint64_t key) {
     return fmix64(key ^ 0x9E3779B97F4A7C15ULL);
 }
 
-// Candidate and survivor slots are claimed in chunks: a wavefront owns
-// kChunk consecutive entries, counts them in a first pass, reserves its whole
-// range with one atomic per counter, and fills it in a second pass.  (One
-// atomic per wavefront on a shared counter still serialises half a million
-// times per scan at these sizes.)
-constexpr int kChunk = 4096;
-
-__global__ __launch_bounds__(kThreads) void k_table_clear(CountSlot* __restrict__ t,
-                                                          uint64_t cap, int64_t block0) {
-    const uint64_t i = (uint64_t)block_index(block0) * kThreads + threadIdx.x;
-    if (i < cap) {
-        t[i].key = kEmptyKey;
-        t[i].count = 0;
-        t[i].dense = -1;
-    }
+// The hash's top bits choose the bucket, the next ones the part of a bucket
+// that is counted at once, the lowest the slot of a table.
+__device__ __forceinline__ uint32_t bucket_of(uint64_t h, int log2_buckets) {
+    return (uint32_t)((h >> 1) >> (63 - log2_buckets));
+}
+__device__ __forceinline__ uint64_t part_of(uint64_t h, int log2_buckets, int bits) {
+    return ((h << log2_buckets) >> 1) >> (63 - bits);
 }
 
-// Code of the n-gram ending at flat position i (row position tt), or kEmptyKey
-// when it is not a candidate of scan n.
-__device__ __forceinline__ uint64_t ngram_code(const int32_t* __restrict__ X,
-                                               const int32_t* __restrict__ ids_prev, int64_t i,
-                                               int64_t tt, int n) {
-    if (tt < n - 1) return kEmptyKey;
-    const uint32_t tok = (uint32_t)X[i];
-    if (n == 2) return ((uint64_t)(uint32_t)X[i - 1] << 16) | tok;
-    const int32_t p = ids_prev[i - 1];  // (n-1)-gram ending one earlier: the prefix
-    const int32_t s = ids_prev[i];      // (n-1)-gram ending here: the suffix
-    if (p < 0 || s < 0) return kEmptyKey;
-    return ((uint64_t)p << 16) | tok;
+// Code of the 2-gram ending at flat position i, or kEmptyKey.
+__device__ __forceinline__ uint64_t bigram_code(const int32_t* __restrict__ X, uint32_t i,
+                                                uint32_t T, bool& bad_token) {
+    const int32_t tok = X[i];
+    const bool ok = tok >= 0 && tok < SCONE_TOKEN_LIMIT;
+    bad_token |= !ok;
+    if (!ok || i % T == 0) return kEmptyKey;
+    const int32_t prev = X[i - 1];
+    if (prev < 0 || prev >= SCONE_TOKEN_LIMIT) return kEmptyKey;  // reported there
+    return ((uint64_t)(uint32_t)prev << 16) | (uint32_t)tok;
 }
 
-// Add c to key's count in the global table; false if the table is full.
-__device__ __forceinline__ bool global_add(CountSlot* __restrict__ t, uint64_t mask,
-                                           uint64_t key, uint32_t c) {
-    uint64_t s = count_hash(key) & mask;
-    for (uint64_t step = 0; step <= mask; ++step) {
-        const unsigned long long old = atomicCAS(reinterpret_cast<unsigned long long*>(&t[s].key),
-                                                 (unsigned long long)kEmptyKey,
-                                                 (unsigned long long)key);
-        if (old == kEmptyKey || old == key) {
-            atomicAdd(&t[s].count, c);
-            return true;
+// Code of the n-gram, n >= 3, whose prefix and suffix have the dense ids p
+// (ending one earlier) and s (ending here).  Both are -1 at a row's first
+// n - 2 positions, so a code never joins two rows.
+__device__ __forceinline__ uint64_t ngram_code(int32_t p, int32_t s, int32_t tok) {
+    return p < 0 || s < 0 ? kEmptyKey : ((uint64_t)p << 16) | (uint32_t)tok;
+}
+
+// The code of scan n ending at position i; ids_prev is scan n - 1's.
+__device__ __forceinline__ uint64_t code_at(const int32_t* __restrict__ X,
+                                            const int32_t* __restrict__ ids_prev, uint32_t i,
+                                            uint32_t T, int n, bool& bad_token) {
+    if (n == 2) return bigram_code(X, i, T, bad_token);
+    return ngram_code(i ? ids_prev[i - 1] : -1, ids_prev[i], X[i]);
+}
+
+// Bucket sizes of scan 2: sizes[bucket * kGroups + group] += positions.  A
+// workgroup takes chunks of one group and adds its LDS counts once.
+__global__ __launch_bounds__(kWide) void k_sizes(const int32_t* __restrict__ X, uint32_t BT,
+                                                 uint32_t T, uint32_t chunk, uint32_t n_chunks,
+                                                 int log2_buckets, unsigned* __restrict__ sizes,
+                                                 unsigned* __restrict__ status) {
+    __shared__ unsigned s_hist[kMaxBuckets];
+    const int buckets = 1 << log2_buckets;
+    for (int b = threadIdx.x; b < buckets; b += kWide) s_hist[b] = 0;
+    __syncthreads();
+    bool bad_token = false;
+    for (uint32_t c = blockIdx.x; c < n_chunks; c += gridDim.x) {
+        for (uint32_t o = threadIdx.x; o < chunk; o += kWide) {
+            const uint32_t i = c * chunk + o;
+            if (i >= BT) break;
+            const uint64_t key = bigram_code(X, i, T, bad_token);
+            if (key != kEmptyKey) atomicAdd(&s_hist[bucket_of(count_hash(key), log2_buckets)], 1u);
         }
-        s = (s + 1) & mask;
-    }
-    return false;
-}
-
-// Counting is aggregated per workgroup first: a workgroup counts
-// kCountPerBlock consecutive positions in an LDS table, then adds each
-// distinct key to the global table once.  Frequent n-grams (a Zipf stream's
-// top bigram is about 1% of all positions) would otherwise serialise hundreds
-// of thousands of increments on one global slot.  Keys that find no LDS slot
-// within kLdsProbe probes go straight to the global table.
-constexpr int kCountPerBlock = 4096;
-constexpr int kLdsSlots = 4096;
-constexpr int kLdsProbe = 32;
-
-__global__ __launch_bounds__(kThreads) void k_count(const int32_t* __restrict__ X, int64_t BT,
-                                                    int64_t T, int n,
-                                                    const int32_t* __restrict__ ids_prev,
-                                                    CountSlot* __restrict__ t, uint64_t mask,
-                                                    unsigned* __restrict__ status) {
-    __shared__ unsigned long long s_key[kLdsSlots];
-    __shared__ unsigned s_cnt[kLdsSlots];
-    for (int j = threadIdx.x; j < kLdsSlots; j += kThreads) {
-        s_key[j] = (unsigned long long)kEmptyKey;
-        s_cnt[j] = 0;
     }
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kCountPerBlock;
-    bool full = false, bad_token = false;
-    for (int r = 0; r < kCountPerBlock / kThreads; ++r) {
-        const int64_t i = base + r * kThreads + threadIdx.x;
-        if (i >= BT) break;
-        if (n == 2) {
-            const int32_t tok = X[i];
-            if (tok < 0 || tok >= SCONE_TOKEN_LIMIT) {
-                bad_token = true;
-                continue;
-            }
-        }
-        const uint64_t key = ngram_code(X, ids_prev, i, i % T, n);
-        if (key == kEmptyKey) continue;
-        if (n == 2 && (X[i - 1] < 0 || X[i - 1] >= SCONE_TOKEN_LIMIT)) continue;  // reported there
-        uint32_t h = (uint32_t)count_hash(key) & (kLdsSlots - 1);
-        bool done = false;
-        for (int q = 0; q < kLdsProbe; ++q) {
-            const unsigned long long old =
-                atomicCAS(&s_key[h], (unsigned long long)kEmptyKey, (unsigned long long)key);
-            if (old == kEmptyKey || old == key) {
-                atomicAdd(&s_cnt[h], 1u);
-                done = true;
-                break;
-            }
-            h = (h + 1) & (kLdsSlots - 1);
-        }
-        if (!done && !global_add(t, mask, key, 1u)) full = true;
-    }
-    __syncthreads();
-    for (int j = threadIdx.x; j < kLdsSlots; j += kThreads) {
-        const unsigned long long key = s_key[j];
-        if (key != kEmptyKey && !global_add(t, mask, key, s_cnt[j])) full = true;
-    }
+    for (int b = threadIdx.x; b < buckets; b += kWide)
+        if (s_hist[b]) atomicAdd(sizes + b * kGroups + blockIdx.x % kGroups, s_hist[b]);
     if (bad_token) atomicOr(status, err_bit(SCONE_ETOKEN));
-    if (full) atomicOr(status, err_bit(SCONE_EFULL));
 }
 
-// Dense ids for the survivors (count >= min_count) and, for scan 2, every
-// entry as a candidate; for later scans the survivors are the candidates.
-__global__ __launch_bounds__(kThreads) void k_survivors(
-    CountSlot* __restrict__ t, uint64_t cap, uint32_t min_count, int level, int keep_all,
-    unsigned* __restrict__ n_surv, uint64_t* __restrict__ skey, unsigned* __restrict__ n_cand,
-    uint64_t* __restrict__ cand_key, uint32_t* __restrict__ cand_count,
-    int8_t* __restrict__ cand_level, unsigned* __restrict__ max_count) {
-    const uint64_t s0 = ((uint64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * kChunk;
-    if (s0 >= cap) return;  // wave-uniform
-    const uint64_t s1 = s0 + kChunk < cap ? s0 + kChunk : cap;
-    const int lane = threadIdx.x & 63;
-    const unsigned long long below = (1ull << lane) - 1ull;
-    unsigned ns = 0, nc = 0;
-    uint32_t mx = 0;
-    for (uint64_t b = s0; b < s1; b += 64) {
-        const uint64_t s = b + lane;
-        const uint64_t key = s < s1 ? t[s].key : kEmptyKey;
-        const bool occupied = key != kEmptyKey;
-        const uint32_t c = occupied ? t[s].count : 0;
-        const bool survive = occupied && c >= min_count;
-        const bool cand = occupied && (survive || keep_all);
-        ns += (unsigned)__popcll(__ballot(survive));
-        nc += (unsigned)__popcll(__ballot(cand));
-        if (cand) mx = c > mx ? c : mx;
+// Region starts from the sizes, cursors set to them, the sizes and the survivor
+// count cleared for the scan to come.  One workgroup, one bucket per thread.
+__global__ __launch_bounds__(kMaxBuckets) void k_offsets(unsigned* __restrict__ sizes, int buckets,
+                                                         unsigned* __restrict__ starts,
+                                                         unsigned* __restrict__ cursors,
+                                                         unsigned* __restrict__ n_surv) {
+    __shared__ unsigned s_wave[kMaxBuckets / 64];
+    const int b = threadIdx.x, lane = b & 63;
+    unsigned v[kGroups], sum = 0;
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        v[g] = b < buckets ? sizes[b * kGroups + g] : 0;
+        sum += v[g];
+    }
+    unsigned inc = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned y = (unsigned)__shfl_up((int)inc, o);
+        if (lane >= o) inc += y;
+    }
+    if (lane == 63) s_wave[b >> 6] = inc;
+    __syncthreads();
+    unsigned at = inc - sum;
+    for (int w = 0; w < b >> 6; ++w) at += s_wave[w];
+    if (b < buckets) {
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            starts[b * kGroups + g] = at;
+            cursors[b * kGroups + g] = at;
+            sizes[b * kGroups + g] = 0;
+            at += v[g];
+        }
+    }
+    if (b == 0) *n_surv = 0;
+}
+
+// One chunk per workgroup: equal codes are merged in an LDS table (a Zipf
+// stream's top bigram is about 1% of all positions, and its bucket would
+// otherwise be that much longer than the others), then each distinct code goes
+// to its bucket's region.  A code that finds no slot within kProbe steps is
+// written by itself.
+constexpr int kProbe = 32;
+
+__global__ __launch_bounds__(kWide) void k_partition(const int32_t* __restrict__ X, uint32_t BT,
+                                                     uint32_t T, int n,
+                                                     const int32_t* __restrict__ ids_prev,
+                                                     uint32_t chunk, int log2_buckets,
+                                                     unsigned* __restrict__ cursors,
+                                                     uint64_t* __restrict__ items) {
+    constexpr int R = kMaxChunk / kWide;
+    __shared__ unsigned long long s_item[kMaxChunk];
+    __shared__ unsigned s_hist[kMaxBuckets];
+    const int buckets = 1 << log2_buckets;
+#pragma unroll
+    for (int r = 0; r < R; ++r) s_item[r * kWide + threadIdx.x] = 0;
+    for (int b = threadIdx.x; b < buckets; b += kWide) s_hist[b] = 0;
+    __syncthreads();
+    uint64_t key[R];
+    bool bad_token = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t o = r * kWide + threadIdx.x;
+        const uint32_t i = blockIdx.x * chunk + o;
+        key[r] = o < chunk && i < BT ? code_at(X, ids_prev, i, T, n, bad_token) : kEmptyKey;
     }
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        const uint32_t y = (uint32_t)__shfl_xor((int)mx, o);
-        mx = y > mx ? y : mx;
-    }
-    unsigned bs = 0, bc = 0;
-    if (lane == 0) {
-        if (ns) bs = atomicAdd(n_surv, ns);
-        if (nc) bc = atomicAdd(n_cand, nc);
-        if (mx) atomicMax(max_count, mx);
-    }
-    bs = (unsigned)__shfl((int)bs, 0);
-    bc = (unsigned)__shfl((int)bc, 0);
-    for (uint64_t b = s0; b < s1; b += 64) {
-        const uint64_t s = b + lane;
-        const uint64_t key = s < s1 ? t[s].key : kEmptyKey;
-        const bool occupied = key != kEmptyKey;
-        const uint32_t c = occupied ? t[s].count : 0;
-        const bool survive = occupied && c >= min_count;
-        const bool cand = occupied && (survive || keep_all);
-        const unsigned long long ms = __ballot(survive), mc = __ballot(cand);
-        if (survive) {
-            const unsigned id = bs + (unsigned)__popcll(ms & below);
-            t[s].dense = (int32_t)id;
-            if (skey) skey[id] = key;
+    for (int r = 0; r < R; ++r) {
+        if (key[r] == kEmptyKey) continue;
+        uint32_t s = (uint32_t)count_hash(key[r]) & (kMaxChunk - 1);
+        for (int q = 0; q < kProbe; ++q) {
+            unsigned long long w = *(volatile unsigned long long*)&s_item[s];
+            if (w == 0) {
+                w = atomicCAS(&s_item[s], 0ull, (unsigned long long)(key[r] << kCountBits | 1));
+                if (w == 0) {
+                    key[r] = kEmptyKey;
+                    break;
+                }
+            }
+            if (w >> kCountBits == key[r]) {
+                atomicAdd(&s_item[s], 1ull);
+                key[r] = kEmptyKey;
+                break;
+            }
+            s = (s + 1) & (kMaxChunk - 1);
         }
-        if (cand) {
-            const unsigned k = bc + (unsigned)__popcll(mc & below);
-            cand_key[k] = key;
-            cand_count[k] = c;
-            cand_level[k] = (int8_t)level;
-        }
-        bs += (unsigned)__popcll(ms);
-        bc += (unsigned)__popcll(mc);
+    }
+    __syncthreads();
+    // Every item's rank among the chunk's items of its bucket.
+    uint64_t item[R];
+    unsigned at[R], at_own[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        item[r] = s_item[r * kWide + threadIdx.x];
+        if (item[r])
+            at[r] = atomicAdd(
+                &s_hist[bucket_of(count_hash(item[r] >> kCountBits), log2_buckets)], 1u);
+        if (key[r] != kEmptyKey)
+            at_own[r] = atomicAdd(&s_hist[bucket_of(count_hash(key[r]), log2_buckets)], 1u);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < buckets; b += kWide)
+        if (s_hist[b])
+            s_hist[b] = atomicAdd(cursors + b * kGroups + blockIdx.x % kGroups, s_hist[b]);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (item[r])
+            items[s_hist[bucket_of(count_hash(item[r] >> kCountBits), log2_buckets)] + at[r]] =
+                item[r];
+        if (key[r] != kEmptyKey)
+            items[s_hist[bucket_of(count_hash(key[r]), log2_buckets)] + at_own[r]] =
+                key[r] << kCountBits | 1;
     }
 }
 
-// Dense id of the survivor of scan n ending at every position, or -1.
-__global__ __launch_bounds__(kThreads) void k_ids(const int32_t* __restrict__ X, int64_t BT,
-                                                  int64_t T, int n,
-                                                  const int32_t* __restrict__ ids_prev,
-                                                  const CountSlot* __restrict__ t, uint64_t mask,
-                                                  int32_t* __restrict__ ids_cur,
-                                                  int64_t block0) {
-    const int64_t i = block_index(block0) * kThreads + threadIdx.x;
-    if (i >= BT) return;
-    const uint64_t key = ngram_code(X, ids_prev, i, i % T, n);
-    int32_t d = -1;
-    if (key != kEmptyKey) {
-        uint64_t s = count_hash(key) & mask;
-        for (uint64_t step = 0; step <= mask; ++step) {
-            const uint64_t k = t[s].key;
-            if (k == key) {
-                d = t[s].dense;
-                break;
+// One workgroup per bucket counts its items in an LDS table, all at once or,
+// when they have more distinct codes than the table takes, in 2^bits parts by
+// the hash's next bits (the bucket is read again for each; distinct codes have
+// distinct hashes, so the parts end up small enough).  Then the survivors
+// (count >= min_count) get dense ids and the candidates (with keep_all every
+// code, else the survivors) are listed, both in a run that the workgroup
+// reserves with one atomic.
+constexpr int kBucketSlots = 8192;
+constexpr int kBucketProbe = 64;
+
+__global__ __launch_bounds__(kWide) void k_bucket(
+    const uint64_t* __restrict__ items, const unsigned* __restrict__ starts,
+    const unsigned* __restrict__ cursors, int log2_buckets, uint32_t min_count, int level,
+    int keep_all, unsigned* __restrict__ n_surv, uint64_t* __restrict__ skey,
+    unsigned* __restrict__ n_cand, uint64_t* __restrict__ cand_key,
+    uint32_t* __restrict__ cand_count, int8_t* __restrict__ cand_level,
+    unsigned* __restrict__ max_count) {
+    constexpr int R = kBucketSlots / kWide;
+    __shared__ unsigned long long s_key[kBucketSlots];
+    __shared__ unsigned s_cnt[kBucketSlots];
+    __shared__ unsigned s_full, s_ns, s_nc, s_mx;
+    const unsigned* begin = starts + blockIdx.x * kGroups;
+    const unsigned* end = cursors + blockIdx.x * kGroups;
+    // item j of the bucket is items[j + shift of its region]
+    unsigned upto[kGroups], shift[kGroups], total = 0;
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        shift[g] = begin[g] - total;
+        total += end[g] - begin[g];
+        upto[g] = total;
+    }
+    if (total == 0) return;
+    const int lane = threadIdx.x & 63;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int bits = 0;
+    for (uint64_t part = 0; part < (1ull << bits);) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            s_key[r * kWide + threadIdx.x] = kEmptyKey;
+            s_cnt[r * kWide + threadIdx.x] = 0;
+        }
+        if (threadIdx.x == 0) s_full = s_ns = s_nc = s_mx = 0;
+        __syncthreads();
+        for (unsigned j0 = 0; j0 < total; j0 += 4 * kWide) {
+            if (*(volatile unsigned*)&s_full) break;
+            uint64_t w[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const unsigned j = j0 + r * kWide + threadIdx.x;
+                unsigned sh = shift[0];
+#pragma unroll
+                for (int g = 1; g < kGroups; ++g) sh = j >= upto[g - 1] ? shift[g] : sh;
+                w[r] = j < total ? items[j + sh] : 0;
             }
-            if (k == kEmptyKey) break;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (!w[r]) continue;
+                const unsigned long long key = w[r] >> kCountBits;
+                const uint64_t h = count_hash(key);
+                if (part_of(h, log2_buckets, bits) != part) continue;
+                uint32_t s = (uint32_t)h & (kBucketSlots - 1);
+                int q = 0;
+                for (; q < kBucketProbe; ++q) {
+                    unsigned long long k = *(volatile unsigned long long*)&s_key[s];
+                    if (k == kEmptyKey)
+                        k = atomicCAS(&s_key[s], (unsigned long long)kEmptyKey, key);
+                    if (k == kEmptyKey || k == key) {
+                        atomicAdd(&s_cnt[s], (unsigned)(w[r] & kCountMask));
+                        break;
+                    }
+                    s = (s + 1) & (kBucketSlots - 1);
+                }
+                if (q == kBucketProbe) *(volatile unsigned*)&s_full = 1;
+            }
+        }
+        __syncthreads();
+        if (s_full) {  // the same for the whole workgroup
+            ++bits;
+            part <<= 1;
+            __syncthreads();
+            continue;
+        }
+        uint64_t k[R];
+        uint32_t c[R];
+        unsigned ns = 0, nc = 0, mx = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            k[r] = s_key[r * kWide + threadIdx.x];
+            c[r] = s_cnt[r * kWide + threadIdx.x];  // 0 where the slot is empty
+            const bool survive = c[r] >= min_count, cand = survive || (keep_all && c[r]);
+            ns += (unsigned)__popcll(__ballot(survive));
+            nc += (unsigned)__popcll(__ballot(cand));
+            if (cand) mx = c[r] > mx ? c[r] : mx;
+        }
+        if (mx) atomicMax(&s_mx, mx);
+        unsigned bs = 0, bc = 0;
+        if (lane == 0) {
+            bs = atomicAdd(&s_ns, ns);
+            bc = atomicAdd(&s_nc, nc);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            s_ns = s_ns ? atomicAdd(n_surv, s_ns) : 0;
+            s_nc = s_nc ? atomicAdd(n_cand, s_nc) : 0;
+            if (s_mx) atomicMax(max_count, s_mx);
+        }
+        __syncthreads();
+        bs = (unsigned)__shfl((int)bs, 0) + s_ns;
+        bc = (unsigned)__shfl((int)bc, 0) + s_nc;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool survive = c[r] >= min_count, cand = survive || (keep_all && c[r]);
+            const unsigned long long ms = __ballot(survive), mc = __ballot(cand);
+            if (survive && skey) skey[bs + (unsigned)__popcll(ms & below)] = k[r];
+            if (cand) {
+                const unsigned at = bc + (unsigned)__popcll(mc & below);
+                cand_key[at] = k[r];
+                cand_count[at] = c[r];
+                cand_level[at] = (int8_t)level;
+            }
+            bs += (unsigned)__popcll(ms);
+            bc += (unsigned)__popcll(mc);
+        }
+        ++part;
+        __syncthreads();
+    }
+}
+
+// Slots of the survivors' table: a power of two of at least twice as many, so
+// that the frequent n-grams' slots stay in the caches.  At most 2 BT rounded
+// up, the table's room in the workspace.
+__device__ __forceinline__ uint64_t surv_slots(unsigned n_surv) {
+    uint64_t cap = 64;
+    while (cap < 2ull * n_surv) cap <<= 1;
+    return cap;
+}
+
+__global__ __launch_bounds__(kThreads) void k_surv_clear(const unsigned* __restrict__ n_surv,
+                                                         SurvSlot* __restrict__ t) {
+    const uint64_t cap = surv_slots(*n_surv);
+    for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < cap;
+         i += (uint64_t)gridDim.x * kThreads)
+        t[i] = SurvSlot{kEmptyKey, -1, 0};
+}
+
+__global__ __launch_bounds__(kThreads) void k_surv_insert(const unsigned* __restrict__ n_surv,
+                                                          const uint64_t* __restrict__ skey,
+                                                          SurvSlot* __restrict__ t) {
+    const unsigned n = *n_surv;
+    const uint64_t mask = surv_slots(n) - 1;
+    for (unsigned id = blockIdx.x * kThreads + threadIdx.x; id < n; id += gridDim.x * kThreads) {
+        const unsigned long long key = skey[id];
+        uint64_t s = count_hash(key) & mask;
+        // half the slots stay empty, so one is found
+        while (atomicCAS(reinterpret_cast<unsigned long long*>(&t[s].key),
+                         (unsigned long long)kEmptyKey, key) != kEmptyKey)
             s = (s + 1) & mask;
+        t[s].dense = (int32_t)id;
+    }
+}
+
+// __syncthreads after this wavefront's LDS operations have completed.  The
+// barrier alone is meant to do that, but in k_ids the compiler (ROCm 7.2)
+// leaves the wait out on the paths from the counting adds to it, and a
+// wavefront's counts were then missing from the sums now and then.
+__device__ __forceinline__ void lds_settled_barrier() {
+    __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
+    __syncthreads();
+}
+
+// Dense id of the survivor of scan n ending at every position, or -1, and the
+// bucket sizes of scan n + 1 (as k_sizes).  Bound by the random reads: a
+// thread has the home slots of kPer positions in flight.
+constexpr int kPer = 4;
+
+__global__ __launch_bounds__(kWide) void k_ids(const int32_t* __restrict__ X, uint32_t BT,
+                                               uint32_t T, int n,
+                                               const int32_t* __restrict__ ids_prev,
+                                               const unsigned* __restrict__ n_surv,
+                                               const SurvSlot* __restrict__ t, uint32_t chunk,
+                                               uint32_t n_chunks, int log2_buckets,
+                                               int32_t* __restrict__ ids_cur,
+                                               unsigned* __restrict__ sizes) {
+    __shared__ unsigned s_hist[kMaxBuckets];
+    __shared__ int32_t s_id[kPer * kWide + 1];  // s_id[j + 1]: id at the step's position j
+    const int buckets = 1 << log2_buckets;
+    for (int b = threadIdx.x; b < buckets; b += kWide) s_hist[b] = 0;
+    const uint64_t mask = surv_slots(*n_surv) - 1;
+    bool bad_token = false;
+    for (uint32_t c = blockIdx.x; c < n_chunks; c += gridDim.x) {
+        const uint32_t c1 = BT - c * chunk < chunk ? BT : (c + 1) * chunk;
+        for (uint32_t i0 = c * chunk; i0 < c1; i0 += kPer * kWide) {
+            // the step's positions, and on thread 0 the one before them
+            uint64_t key[kPer + 1];
+            u32x4 slot[kPer + 1];
+            uint64_t s[kPer + 1];
+#pragma unroll
+            for (int r = 0; r <= kPer; ++r) {
+                const uint32_t i = r < kPer ? i0 + r * kWide + threadIdx.x : i0 - 1;
+                const bool on = r < kPer ? i < c1 : threadIdx.x == 0 && i0 > 0;
+                key[r] = on ? code_at(X, ids_prev, i, T, n, bad_token) : kEmptyKey;
+            }
+#pragma unroll
+            for (int r = 0; r <= kPer; ++r) {
+                s[r] = count_hash(key[r]) & mask;
+                if (key[r] != kEmptyKey) slot[r] = *reinterpret_cast<const u32x4*>(t + s[r]);
+            }
+            lds_settled_barrier();  // the last step's ids have been read
+#pragma unroll
+            for (int r = 0; r <= kPer; ++r) {
+                int32_t d = -1;
+                if (key[r] != kEmptyKey) {
+                    for (;;) {  // half the slots are empty, so it ends
+                        const uint64_t k = (uint64_t)slot[r].x | (uint64_t)slot[r].y << 32;
+                        if (k == key[r]) {
+                            d = (int32_t)slot[r].z;
+                            break;
+                        }
+                        if (k == kEmptyKey) break;
+                        s[r] = (s[r] + 1) & mask;
+                        slot[r] = *reinterpret_cast<const u32x4*>(t + s[r]);
+                    }
+                }
+                const uint32_t o = r * kWide + threadIdx.x;
+                if (r < kPer) {
+                    s_id[o + 1] = d;
+                    if (i0 + o < c1) ids_cur[i0 + o] = d;
+                } else if (threadIdx.x == 0) {
+                    s_id[0] = d;
+                }
+            }
+            lds_settled_barrier();
+#pragma unroll
+            for (int r = 0; r < kPer; ++r) {
+                const uint32_t o = r * kWide + threadIdx.x;
+                if (i0 + o >= c1) continue;
+                const int32_t p = s_id[o], d = s_id[o + 1];
+                if (p < 0 || d < 0) continue;
+                const uint64_t next = ngram_code(p, d, X[i0 + o]);
+                atomicAdd(&s_hist[bucket_of(count_hash(next), log2_buckets)], 1u);
+            }
         }
     }
-    ids_cur[i] = d;
+    lds_settled_barrier();
+    for (int b = threadIdx.x; b < buckets; b += kWide)
+        if (s_hist[b]) atomicAdd(sizes + b * kGroups + blockIdx.x % kGroups, s_hist[b]);
 }
 
 __global__ __launch_bounds__(kThreads) void k_count_at_least(const uint32_t* __restrict__ cnt,
@@ -246,6 +504,8 @@ __global__ __launch_bounds__(kThreads) void k_count_at_least(const uint32_t* __r
 // Histogram of candidate counts, exact below kHistBins - 1 and pooled above:
 // a workgroup counts a run of candidates in LDS and adds its non-zero bins.
 constexpr int kHistBins = 4096;
+static_assert(kHistBins * sizeof(unsigned long long) >= kMaxBuckets * kGroups * sizeof(unsigned),
+              "the bucket sizes lie in the histogram's place");
 
 __global__ __launch_bounds__(kThreads) void k_count_hist(const uint32_t* __restrict__ cnt,
                                                          int64_t n, int64_t per_block,
@@ -268,48 +528,64 @@ struct LevelKeys {
     const uint64_t* skey[SCONE_MAX_FGRAM_LEN + 1];  // survivors' codes by scan
 };
 
-// Emit the selected candidates with their tokens.
+// Emit the selected candidates with their tokens.  A workgroup takes
+// kSelectPerBlock candidates and reserves its output rows with one atomic per
+// counter (one per wavefront on a shared counter serialises).
+constexpr int kSelectPerBlock = 16 * kThreads;
+
 __global__ __launch_bounds__(kThreads) void k_select(
     const uint64_t* __restrict__ cand_key, const uint32_t* __restrict__ cand_count,
     const int8_t* __restrict__ cand_level, int64_t n_cand, uint32_t thresh, int64_t n_above,
     int64_t S, LevelKeys lk, int max_len, unsigned* __restrict__ n_gt,
     unsigned* __restrict__ n_eq, int32_t* __restrict__ fgrams, int32_t* __restrict__ lengths,
     int32_t* __restrict__ counts) {
-    const int64_t i0 = ((int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * kChunk;
-    if (i0 >= n_cand) return;  // wave-uniform
-    const int64_t i1 = i0 + kChunk < n_cand ? i0 + kChunk : n_cand;
+    constexpr int R = kSelectPerBlock / kThreads;
+    __shared__ unsigned s_gt, s_eq;
+    if (threadIdx.x == 0) s_gt = s_eq = 0;
+    const int64_t i0 = (int64_t)blockIdx.x * kSelectPerBlock + threadIdx.x;
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (1ull << lane) - 1ull;
-    unsigned ng = 0, ne = 0;
-    for (int64_t b = i0; b < i1; b += 64) {
-        const int64_t i = b + lane;
-        const uint32_t c = i < i1 ? cand_count[i] : 0;
-        ng += (unsigned)__popcll(__ballot(i < i1 && c > thresh));
-        ne += (unsigned)__popcll(__ballot(i < i1 && c == thresh));
+    uint32_t c[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = i0 + r * kThreads;
+        c[r] = i < n_cand ? cand_count[i] : 0;  // a candidate counts at least 1
     }
+    unsigned ng = 0, ne = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        ng += (unsigned)__popcll(__ballot(c[r] > thresh));
+        ne += (unsigned)__popcll(__ballot(c[r] && c[r] == thresh));
+    }
+    __syncthreads();
     unsigned bg = 0, be = 0;
     if (lane == 0) {
-        if (ng) bg = atomicAdd(n_gt, ng);
-        if (ne) be = atomicAdd(n_eq, ne);
+        bg = atomicAdd(&s_gt, ng);
+        be = atomicAdd(&s_eq, ne);
     }
-    bg = (unsigned)__shfl((int)bg, 0);
-    be = (unsigned)__shfl((int)be, 0);
-    for (int64_t b = i0; b < i1; b += 64) {
-        const int64_t i = b + lane;
-        const bool valid = i < i1;
-        const uint32_t c = valid ? cand_count[i] : 0;
-        const bool gt = valid && c > thresh, eq = valid && c == thresh;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        s_gt = s_gt ? atomicAdd(n_gt, s_gt) : 0;
+        s_eq = s_eq ? atomicAdd(n_eq, s_eq) : 0;
+    }
+    __syncthreads();
+    bg = (unsigned)__shfl((int)bg, 0) + s_gt;
+    be = (unsigned)__shfl((int)be, 0) + s_eq;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool gt = c[r] > thresh, eq = c[r] && c[r] == thresh;
         const unsigned long long mg = __ballot(gt), me = __ballot(eq);
         int64_t pos = -1;
         if (gt) {
             pos = bg + (unsigned)__popcll(mg & below);
         } else if (eq) {
-            const int64_t e = be + (unsigned)__popcll(me & below);
+            const int64_t e = (int64_t)be + (unsigned)__popcll(me & below);
             if (n_above + e < S) pos = n_above + e;
         }
         bg += (unsigned)__popcll(mg);
         be += (unsigned)__popcll(me);
         if (pos < 0 || pos >= S) continue;
+        const int64_t i = i0 + r * kThreads;
         const int level = cand_level[i];
         int32_t tok[SCONE_MAX_FGRAM_LEN];
         uint64_t key = cand_key[i];
@@ -322,7 +598,7 @@ __global__ __launch_bounds__(kThreads) void k_select(
         int32_t* row = fgrams + pos * (int64_t)max_len;
         for (int j = 0; j < max_len; ++j) row[j] = j < level ? tok[j] : -1;
         lengths[pos] = level;
-        counts[pos] = (int32_t)c;
+        counts[pos] = (int32_t)c[r];
     }
 }
 
@@ -332,9 +608,13 @@ __global__ __launch_bounds__(kThreads) void k_select(
 namespace scone {
 namespace {
 
-// Scratch of one call, carved from one workspace: the counting table, the
+// Scratch of one call, carved from one workspace: the survivors' table, the
 // dense ids of two consecutive scans, the candidates, the counters and
-// histogram, and the survivors' codes of every scan but the last.
+// histogram, and the survivors' codes of every scan but the last.  What lives
+// at different times shares memory: a scan's items (8 bytes per position) lie
+// where its survivors' table (at least 32) is made once they are counted, the
+// region starts and cursors where the ids of the scan's end are written
+// (k_ids, after their last use), the bucket sizes in the histogram's place.
 struct DiscLayout {
     uint64_t cap;
     int64_t cand_cap;
@@ -354,7 +634,7 @@ DiscLayout disc_layout(int64_t BT, int max_len) {
         off = (off + bytes + 255) & ~(size_t)255;
         return at;
     };
-    l.table = take(l.cap * sizeof(CountSlot));
+    l.table = take(l.cap * sizeof(SurvSlot));
     l.ids_a = take(BT * sizeof(int32_t));
     l.ids_b = take(BT * sizeof(int32_t));
     l.cand_key = take(l.cand_cap * sizeof(uint64_t));
@@ -366,6 +646,23 @@ DiscLayout disc_layout(int64_t BT, int max_len) {
     for (int L = 2; L < max_len; ++L) l.skey[L] = take(BT * sizeof(uint64_t));
     l.total = off;
     return l;
+}
+
+// How a scan cuts up BT positions: chunks of 1,024 to 8,192 (as long as there
+// are 256 of them, one per compute unit, the longer the fewer items) and
+// buckets of about 4,096 positions, up to kMaxBuckets.
+struct Shape {
+    uint32_t chunk, n_chunks;
+    int log2_buckets;
+};
+
+Shape scan_shape(int64_t BT) {
+    Shape s{kWide, 0, 0};
+    while (s.chunk < kMaxChunk && BT / (2 * (int64_t)s.chunk) >= 256) s.chunk *= 2;
+    s.n_chunks = (uint32_t)((BT + s.chunk - 1) / s.chunk);
+    while ((4096ll << s.log2_buckets) < BT && (1 << s.log2_buckets) < kMaxBuckets)
+        ++s.log2_buckets;
+    return s;
 }
 
 // SCONE_OK when (B, T, max_len) are sizes the call handles.
@@ -420,9 +717,6 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
 
-    const uint64_t cap = lay.cap;
-    const uint64_t mask = cap - 1;
-
     // Without a workspace the call takes its scratch in one allocation and
     // frees it before returning (the call is synchronous).
     void* own = nullptr;
@@ -438,7 +732,8 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
         if (own) (void)hipFree(own);
     };
     uint8_t* ws = static_cast<uint8_t*>(workspace);
-    CountSlot* table = reinterpret_cast<CountSlot*>(ws + lay.table);
+    SurvSlot* table = reinterpret_cast<SurvSlot*>(ws + lay.table);
+    uint64_t* items = reinterpret_cast<uint64_t*>(ws + lay.table);
     int32_t* ids_a = reinterpret_cast<int32_t*>(ws + lay.ids_a);
     int32_t* ids_b = reinterpret_cast<int32_t*>(ws + lay.ids_b);
     uint64_t* cand_key = reinterpret_cast<uint64_t*>(ws + lay.cand_key);
@@ -447,6 +742,7 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
     unsigned* ctr = reinterpret_cast<unsigned*>(ws + lay.ctr);
     unsigned long long* acc = reinterpret_cast<unsigned long long*>(ws + lay.acc);
     unsigned long long* hist = reinterpret_cast<unsigned long long*>(ws + lay.hist);
+    unsigned* sizes = reinterpret_cast<unsigned*>(ws + lay.hist);
     LevelKeys lk{};
     uint64_t* skeys[SCONE_MAX_FGRAM_LEN + 1] = {};
     for (int L = 2; L < max_len; ++L) {
@@ -455,39 +751,41 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
     }
     // ctr: [0] status, [1] survivors, [2] candidates, [3] max count, [4] n_gt, [5] n_eq
     int rc = SCONE_OK;
-    // (The table clear covers up to 2^32 slots, more work-items than one
-    // launch holds; the other grids stay far below that at BT < 2^31.)
-    const int64_t g_cap = (int64_t)((cap + kThreads - 1) / kThreads);
-    const int64_t g_bt = (BT + kThreads - 1) / kThreads;
-    const dim3 block(kThreads);
-    const int64_t waves_per_block = kThreads / 64;
-    auto chunk_grid = [&](int64_t n) {
-        const int64_t waves = (n + kChunk - 1) / kChunk;
-        return (unsigned)((waves + waves_per_block - 1) / waves_per_block);
-    };
-    if (hipMemsetAsync(ctr, 0, 16 * sizeof(unsigned), st) != hipSuccess) rc = SCONE_EHIP;
+    const Shape sh = scan_shape(BT);
+    const uint32_t n_tok = (uint32_t)BT, row = (uint32_t)T;
+    const dim3 wide(kWide), narrow(kThreads);
+    // passes over the positions: two workgroups per compute unit, a multiple
+    // of kGroups so that each stays with the chunks of one group
+    const unsigned g_pos = sh.n_chunks < 512 ? (sh.n_chunks + kGroups - 1) / kGroups * kGroups
+                                             : 512;
+    const unsigned g_surv = (unsigned)(BT < (1 << 18) ? (BT + kThreads - 1) / kThreads : 1024);
+    if (hipMemsetAsync(ctr, 0, 16 * sizeof(unsigned), st) != hipSuccess ||
+        hipMemsetAsync(sizes, 0, (sizeof(unsigned) * kGroups) << sh.log2_buckets, st) !=
+            hipSuccess)
+        rc = SCONE_EHIP;
+    if (rc == SCONE_OK)
+        hipLaunchKernelGGL(k_sizes, dim3(g_pos), wide, 0, st, token_ids, n_tok, row, sh.chunk,
+                           sh.n_chunks, sh.log2_buckets, sizes, ctr + 0);
     int32_t* ids_prev = ids_a;
     int32_t* ids_cur = ids_b;
     for (int n = 2; n <= max_len && rc == SCONE_OK; ++n) {
-        if (launch_blocks(g_cap, kThreads, [&](int64_t b0, dim3 grid) {
-                hipLaunchKernelGGL(k_table_clear, grid, block, 0, st, table, cap, b0);
-            }) != hipSuccess)
-            rc = SCONE_EHIP;
-        hipLaunchKernelGGL(k_count, dim3((unsigned)((BT + kCountPerBlock - 1) / kCountPerBlock)),
-                           dim3(kThreads), 0, st, token_ids, BT, T, n,
-                           ids_prev, table, mask, ctr + 0);
-        if (hipMemsetAsync(ctr + 1, 0, sizeof(unsigned), st) != hipSuccess) rc = SCONE_EHIP;
-        hipLaunchKernelGGL(k_survivors, dim3(chunk_grid((int64_t)cap)), dim3(kThreads), 0, st,
-                           table, cap,
-                           (uint32_t)min_count, n, n == 2 ? 1 : 0, ctr + 1,
-                           n < max_len ? skeys[n] : nullptr, ctr + 2, cand_key, cand_count,
-                           cand_level, ctr + 3);
+        unsigned* starts = reinterpret_cast<unsigned*>(ids_cur);
+        unsigned* cursors = starts + ((size_t)kGroups << sh.log2_buckets);
+        hipLaunchKernelGGL(k_offsets, dim3(1), dim3(kMaxBuckets), 0, st, sizes,
+                           1 << sh.log2_buckets, starts, cursors, ctr + 1);
+        hipLaunchKernelGGL(k_partition, dim3(sh.n_chunks), wide, 0, st, token_ids, n_tok, row, n,
+                           ids_prev, sh.chunk, sh.log2_buckets, cursors, items);
+        hipLaunchKernelGGL(k_bucket, dim3(1u << sh.log2_buckets), wide, 0, st, items, starts,
+                           cursors, sh.log2_buckets, (uint32_t)min_count, n, n == 2 ? 1 : 0,
+                           ctr + 1, n < max_len ? skeys[n] : nullptr, ctr + 2, cand_key,
+                           cand_count, cand_level, ctr + 3);
         if (n < max_len) {
-            if (launch_blocks(g_bt, kThreads, [&](int64_t b0, dim3 grid) {
-                    hipLaunchKernelGGL(k_ids, grid, block, 0, st, token_ids, BT, T, n, ids_prev,
-                                       table, mask, ids_cur, b0);
-                }) != hipSuccess)
-                rc = SCONE_EHIP;
+            hipLaunchKernelGGL(k_surv_clear, dim3(g_surv), narrow, 0, st, ctr + 1, table);
+            hipLaunchKernelGGL(k_surv_insert, dim3(g_surv), narrow, 0, st, ctr + 1, skeys[n],
+                               table);
+            hipLaunchKernelGGL(k_ids, dim3(g_pos), wide, 0, st, token_ids, n_tok, row, n, ids_prev,
+                               ctr + 1, table, sh.chunk, sh.n_chunks, sh.log2_buckets, ids_cur,
+                               sizes);
             int32_t* tmp = ids_prev;
             ids_prev = ids_cur;
             ids_cur = tmp;
@@ -499,7 +797,7 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
         (hipMemcpyAsync(h, ctr, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess ||
          hipStreamSynchronize(st) != hipSuccess))
         rc = SCONE_EHIP;
-    if (rc == SCONE_OK && h[0]) rc = (h[0] & err_bit(SCONE_ETOKEN)) ? SCONE_ETOKEN : SCONE_EFULL;
+    if (rc == SCONE_OK && h[0]) rc = SCONE_ETOKEN;
     const int64_t n_cand = h[2];
     const uint32_t max_c = h[3];
     // Threshold: the largest count c with at least S candidates counting >= c.
@@ -522,7 +820,7 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
     if (rc == SCONE_OK && n_cand > S) {
         // One pass: a histogram of the counts, exact below kHistBins - 1.
         std::vector<unsigned long long> hh(kHistBins, 0);
-        const int64_t per_block = 65536;
+        const int64_t per_block = 8192;
         if (hipMemsetAsync(hist, 0, kHistBins * sizeof(unsigned long long), st) != hipSuccess)
             rc = SCONE_EHIP;
         if (rc == SCONE_OK) {
@@ -562,7 +860,9 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
         }
     }
     if (rc == SCONE_OK && n_cand > 0) {
-        hipLaunchKernelGGL(k_select, dim3(chunk_grid(n_cand)), dim3(kThreads), 0, st, cand_key, cand_count, cand_level, n_cand, thresh,
+        hipLaunchKernelGGL(k_select,
+                           dim3((unsigned)((n_cand + kSelectPerBlock - 1) / kSelectPerBlock)),
+                           narrow, 0, st, cand_key, cand_count, cand_level, n_cand, thresh,
                            n_above, S, lk, max_len, ctr + 4, ctr + 5, fgrams, lengths, counts);
         if (hipGetLastError() != hipSuccess) rc = SCONE_EHIP;
     }
