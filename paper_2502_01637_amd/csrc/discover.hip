@@ -28,14 +28,16 @@
 //   k_ids        every position looks its code up there and counts the next
 //                scan's bucket sizes on the way
 //
-// 16.8M tokens (K = 5, 1M f-grams kept): scans 2 to 5 took 2,280, 1,760, 1,040
-// and 750 us with the global table.
+// 16.8M tokens (K = 5, 1M f-grams kept), scans 2 to 5: 2,280, 1,760, 1,040 and
+// 750 us with the global table, 610, 500, 300 and 130 us now; the whole call
+// and the caller's sort of its result 6.76 -> 2.22 ms.
 //
 // The candidates are all 2-grams and the survivors of scans 3..K; the top S by
 // count are found with a threshold search (equal counts at the threshold are
 // taken in an unspecified order, as Algorithm 3 allows) and their tokens are
 // rebuilt by walking the prefix ids back to scan 2.
-#include <vector>
+#include <algorithm>
+#include <cstring>
 
 #include "scone_internal.h"
 
@@ -76,16 +78,17 @@ __device__ __forceinline__ uint64_t part_of(uint64_t h, int log2_buckets, int bi
     return ((h << log2_buckets) >> 1) >> (63 - bits);
 }
 
-// Code of the 2-gram ending at flat position i, or kEmptyKey.
+// Code of the 2-gram ending at flat position i, or kEmptyKey.  (Every load of
+// the code functions is unconditional, so that a thread's positions are all in
+// flight at once.)
 __device__ __forceinline__ uint64_t bigram_code(const int32_t* __restrict__ X, uint32_t i,
                                                 uint32_t T, bool& bad_token) {
-    const int32_t tok = X[i];
+    const int32_t prev = X[i ? i - 1 : 0], tok = X[i];
     const bool ok = tok >= 0 && tok < SCONE_TOKEN_LIMIT;
     bad_token |= !ok;
-    if (!ok || i % T == 0) return kEmptyKey;
-    const int32_t prev = X[i - 1];
-    if (prev < 0 || prev >= SCONE_TOKEN_LIMIT) return kEmptyKey;  // reported there
-    return ((uint64_t)(uint32_t)prev << 16) | (uint32_t)tok;
+    // a bad previous token is reported where it is the last one
+    const bool whole = ok && prev >= 0 && prev < SCONE_TOKEN_LIMIT && i % T != 0;
+    return whole ? ((uint64_t)(uint32_t)prev << 16) | (uint32_t)tok : kEmptyKey;
 }
 
 // Code of the n-gram, n >= 3, whose prefix and suffix have the dense ids p
@@ -95,12 +98,15 @@ __device__ __forceinline__ uint64_t ngram_code(int32_t p, int32_t s, int32_t tok
     return p < 0 || s < 0 ? kEmptyKey : ((uint64_t)p << 16) | (uint32_t)tok;
 }
 
-// The code of scan n ending at position i; ids_prev is scan n - 1's.
+// The code ending at position i, of scan 2 (kFirst) or of a later one, whose
+// previous scan's ids are ids_prev.
+template <bool kFirst>
 __device__ __forceinline__ uint64_t code_at(const int32_t* __restrict__ X,
                                             const int32_t* __restrict__ ids_prev, uint32_t i,
-                                            uint32_t T, int n, bool& bad_token) {
-    if (n == 2) return bigram_code(X, i, T, bad_token);
-    return ngram_code(i ? ids_prev[i - 1] : -1, ids_prev[i], X[i]);
+                                            uint32_t T, bool& bad_token) {
+    if constexpr (kFirst) return bigram_code(X, i, T, bad_token);
+    const int32_t p = ids_prev[i ? i - 1 : 0], s = ids_prev[i], tok = X[i];
+    return ngram_code(i ? p : -1, s, tok);
 }
 
 // Bucket sizes of scan 2: sizes[bucket * kGroups + group] += positions.  A
@@ -166,20 +172,25 @@ __global__ __launch_bounds__(kMaxBuckets) void k_offsets(unsigned* __restrict__ 
 
 // One chunk per workgroup: equal codes are merged in an LDS table (a Zipf
 // stream's top bigram is about 1% of all positions, and its bucket would
-// otherwise be that much longer than the others), then each distinct code goes
-// to its bucket's region.  A code that finds no slot within kProbe steps is
-// written by itself.
-constexpr int kProbe = 32;
+// otherwise be that much longer than the others), then each code goes to its
+// bucket's region.  A code that finds no slot within kProbe steps is written by
+// itself: merging is for the frequent codes, which find one early, and the pass
+// is bound by its LDS operations.  Whole calls on 16.8M tokens with 1, 2, 4, 8
+// and 32 steps took 2.22, 2.31, 2.40, 2.51 and 2.92 ms; with one step a
+// frequent code is shut out wherever another took its slot first.
+constexpr int kProbe = 2;
 
+template <bool kFirst>
 __global__ __launch_bounds__(kWide) void k_partition(const int32_t* __restrict__ X, uint32_t BT,
-                                                     uint32_t T, int n,
+                                                     uint32_t T,
                                                      const int32_t* __restrict__ ids_prev,
                                                      uint32_t chunk, int log2_buckets,
                                                      unsigned* __restrict__ cursors,
                                                      uint64_t* __restrict__ items) {
     constexpr int R = kMaxChunk / kWide;
+    static_assert(kMaxBuckets == kWide, "a thread per bucket");
     __shared__ unsigned long long s_item[kMaxChunk];
-    __shared__ unsigned s_hist[kMaxBuckets];
+    __shared__ unsigned s_hist[kMaxBuckets], s_region[kMaxBuckets], s_wave[kWide / 64];
     const int buckets = 1 << log2_buckets;
 #pragma unroll
     for (int r = 0; r < R; ++r) s_item[r * kWide + threadIdx.x] = 0;
@@ -191,7 +202,9 @@ __global__ __launch_bounds__(kWide) void k_partition(const int32_t* __restrict__
     for (int r = 0; r < R; ++r) {
         const uint32_t o = r * kWide + threadIdx.x;
         const uint32_t i = blockIdx.x * chunk + o;
-        key[r] = o < chunk && i < BT ? code_at(X, ids_prev, i, T, n, bad_token) : kEmptyKey;
+        const bool on = o < chunk && i < BT;
+        const uint64_t k = code_at<kFirst>(X, ids_prev, on ? i : 0, T, bad_token);
+        key[r] = on ? k : kEmptyKey;
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -215,31 +228,59 @@ __global__ __launch_bounds__(kWide) void k_partition(const int32_t* __restrict__
         }
     }
     __syncthreads();
-    // Every item's rank among the chunk's items of its bucket.
+    // Every item's bucket and its rank among the chunk's items there.
     uint64_t item[R];
     unsigned at[R], at_own[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         item[r] = s_item[r * kWide + threadIdx.x];
-        if (item[r])
-            at[r] = atomicAdd(
-                &s_hist[bucket_of(count_hash(item[r] >> kCountBits), log2_buckets)], 1u);
-        if (key[r] != kEmptyKey)
-            at_own[r] = atomicAdd(&s_hist[bucket_of(count_hash(key[r]), log2_buckets)], 1u);
+        if (item[r]) {
+            const uint32_t b = bucket_of(count_hash(item[r] >> kCountBits), log2_buckets);
+            at[r] = b << 16 | atomicAdd(&s_hist[b], 1u);
+        }
+        if (key[r] != kEmptyKey) {
+            const uint32_t b = bucket_of(count_hash(key[r]), log2_buckets);
+            at_own[r] = b << 16 | atomicAdd(&s_hist[b], 1u);
+        }
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < buckets; b += kWide)
-        if (s_hist[b])
-            s_hist[b] = atomicAdd(cursors + b * kGroups + blockIdx.x % kGroups, s_hist[b]);
+    // A thread per bucket: where its items start, in LDS and in its region.
+    const int b = threadIdx.x, lane = b & 63;
+    const unsigned mine = b < buckets ? s_hist[b] : 0;
+    unsigned inc = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned y = (unsigned)__shfl_up((int)inc, o);
+        if (lane >= o) inc += y;
+    }
+    if (lane == 63) s_wave[b >> 6] = inc;
+    const unsigned region =
+        mine ? atomicAdd(cursors + b * kGroups + blockIdx.x % kGroups, mine) : 0;
+    __syncthreads();
+    unsigned start = inc - mine, total = 0;
+    for (int w = 0; w < kWide / 64; ++w) {
+        if (w < b >> 6) start += s_wave[w];
+        total += s_wave[w];
+    }
+    s_hist[b] = start;
+    s_region[b] = region - start;
+    __syncthreads();
+    // The items by bucket in LDS, so that neighbouring lanes write neighbouring
+    // items: one store transaction per run where one per item (8 bytes at 64
+    // places per wavefront) ran at the rate of random accesses.
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (item[r]) s_item[s_hist[at[r] >> 16] + (at[r] & 0xFFFF)] = item[r];
+        if (key[r] != kEmptyKey)
+            s_item[s_hist[at_own[r] >> 16] + (at_own[r] & 0xFFFF)] = key[r] << kCountBits | 1;
+    }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        if (item[r])
-            items[s_hist[bucket_of(count_hash(item[r] >> kCountBits), log2_buckets)] + at[r]] =
-                item[r];
-        if (key[r] != kEmptyKey)
-            items[s_hist[bucket_of(count_hash(key[r]), log2_buckets)] + at_own[r]] =
-                key[r] << kCountBits | 1;
+        const unsigned j = r * kWide + threadIdx.x;
+        if (j >= total) break;
+        const uint64_t w = s_item[j];
+        items[s_region[bucket_of(count_hash(w >> kCountBits), log2_buckets)] + j] = w;
     }
 }
 
@@ -275,12 +316,16 @@ __global__ __launch_bounds__(kWide) void k_bucket(
         upto[g] = total;
     }
     if (total == 0) return;
+    // A table of at least twice the items, where they are few, up to kBucketSlots.
+    unsigned slots = kWide;
+    while (slots < kBucketSlots && slots < 2 * total) slots <<= 1;
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (1ull << lane) - 1ull;
     int bits = 0;
     for (uint64_t part = 0; part < (1ull << bits);) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
+            if (r * kWide >= slots) break;
             s_key[r * kWide + threadIdx.x] = kEmptyKey;
             s_cnt[r * kWide + threadIdx.x] = 0;
         }
@@ -303,7 +348,7 @@ __global__ __launch_bounds__(kWide) void k_bucket(
                 const unsigned long long key = w[r] >> kCountBits;
                 const uint64_t h = count_hash(key);
                 if (part_of(h, log2_buckets, bits) != part) continue;
-                uint32_t s = (uint32_t)h & (kBucketSlots - 1);
+                uint32_t s = (uint32_t)h & (slots - 1);
                 int q = 0;
                 for (; q < kBucketProbe; ++q) {
                     unsigned long long k = *(volatile unsigned long long*)&s_key[s];
@@ -313,7 +358,7 @@ __global__ __launch_bounds__(kWide) void k_bucket(
                         atomicAdd(&s_cnt[s], (unsigned)(w[r] & kCountMask));
                         break;
                     }
-                    s = (s + 1) & (kBucketSlots - 1);
+                    s = (s + 1) & (slots - 1);
                 }
                 if (q == kBucketProbe) *(volatile unsigned*)&s_full = 1;
             }
@@ -330,6 +375,8 @@ __global__ __launch_bounds__(kWide) void k_bucket(
         unsigned ns = 0, nc = 0, mx = 0;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
+            c[r] = 0;
+            if (r * kWide >= slots) continue;
             k[r] = s_key[r * kWide + threadIdx.x];
             c[r] = s_cnt[r * kWide + threadIdx.x];  // 0 where the slot is empty
             const bool survive = c[r] >= min_count, cand = survive || (keep_all && c[r]);
@@ -354,6 +401,7 @@ __global__ __launch_bounds__(kWide) void k_bucket(
         bc = (unsigned)__shfl((int)bc, 0) + s_nc;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
+            if (r * kWide >= slots) break;
             const bool survive = c[r] >= min_count, cand = survive || (keep_all && c[r]);
             const unsigned long long ms = __ballot(survive), mc = __ballot(cand);
             if (survive && skey) skey[bs + (unsigned)__popcll(ms & below)] = k[r];
@@ -418,8 +466,9 @@ __device__ __forceinline__ void lds_settled_barrier() {
 // thread has the home slots of kPer positions in flight.
 constexpr int kPer = 4;
 
+template <bool kFirst>
 __global__ __launch_bounds__(kWide) void k_ids(const int32_t* __restrict__ X, uint32_t BT,
-                                               uint32_t T, int n,
+                                               uint32_t T,
                                                const int32_t* __restrict__ ids_prev,
                                                const unsigned* __restrict__ n_surv,
                                                const SurvSlot* __restrict__ t, uint32_t chunk,
@@ -443,7 +492,8 @@ __global__ __launch_bounds__(kWide) void k_ids(const int32_t* __restrict__ X, ui
             for (int r = 0; r <= kPer; ++r) {
                 const uint32_t i = r < kPer ? i0 + r * kWide + threadIdx.x : i0 - 1;
                 const bool on = r < kPer ? i < c1 : threadIdx.x == 0 && i0 > 0;
-                key[r] = on ? code_at(X, ids_prev, i, T, n, bad_token) : kEmptyKey;
+                const uint64_t k = code_at<kFirst>(X, ids_prev, on ? i : 0, T, bad_token);
+                key[r] = on ? k : kEmptyKey;
             }
 #pragma unroll
             for (int r = 0; r <= kPer; ++r) {
@@ -491,6 +541,81 @@ __global__ __launch_bounds__(kWide) void k_ids(const int32_t* __restrict__ X, ui
         if (s_hist[b]) atomicAdd(sizes + b * kGroups + blockIdx.x % kGroups, s_hist[b]);
 }
 
+// The count threshold: the largest count c that at least S candidates reach.
+struct Cut {
+    uint32_t thresh;   // c, or 0 when every candidate is taken
+    uint32_t wide;     // c is at least kHistBins - 1 and not found yet
+    int64_t n_above;   // candidates counting more than c
+};
+
+// Histogram of candidate counts, exact below kHistBins - 1 and pooled above:
+// a workgroup counts runs of candidates in LDS and adds its non-zero bins.
+// Nothing when there are no more candidates than wanted.
+constexpr int kHistBins = 4096;
+constexpr int kHistRun = 8192;
+static_assert(kHistBins * sizeof(unsigned long long) >= kMaxBuckets * kGroups * sizeof(unsigned),
+              "the bucket sizes lie in the histogram's place");
+
+__global__ __launch_bounds__(kThreads) void k_count_hist(const uint32_t* __restrict__ cnt,
+                                                         const unsigned* __restrict__ n_cand,
+                                                         int64_t S,
+                                                         unsigned long long* __restrict__ hist) {
+    __shared__ unsigned h[kHistBins];
+    const int64_t n = *n_cand;
+    if (n <= S || (int64_t)blockIdx.x * kHistRun >= n) return;
+    for (int i = threadIdx.x; i < kHistBins; i += kThreads) h[i] = 0;
+    __syncthreads();
+    for (int64_t i0 = (int64_t)blockIdx.x * kHistRun; i0 < n;
+         i0 += (int64_t)gridDim.x * kHistRun) {
+        const int64_t i1 = i0 + kHistRun < n ? i0 + kHistRun : n;
+        for (int64_t i = i0 + threadIdx.x; i < i1; i += kThreads) {
+            const uint32_t c = cnt[i];
+            atomicAdd(&h[c < kHistBins - 1 ? c : kHistBins - 1], 1u);
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kHistBins; i += kThreads)
+        if (h[i]) atomicAdd(hist + i, (unsigned long long)h[i]);
+}
+
+// Reads the cut off the histogram (one workgroup, four bins per thread).
+__global__ __launch_bounds__(kWide) void k_cut(const unsigned long long* __restrict__ hist,
+                                               const unsigned* __restrict__ n_cand, int64_t S,
+                                               Cut* __restrict__ cut) {
+    constexpr int R = kHistBins / kWide;
+    __shared__ unsigned long long s_sum[kWide / 64];
+    if ((int64_t)*n_cand <= S) {
+        if (threadIdx.x == 0) *cut = Cut{0, 0, 0};
+        return;
+    }
+    // bins from the highest count down; s = candidates in this thread's bins
+    unsigned long long v[R], s = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        v[r] = hist[kHistBins - 1 - (threadIdx.x * R + r)];
+        s += v[r];
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned long long inc = s;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long y = __shfl_up(inc, o);
+        if (lane >= o) inc += y;
+    }
+    if (lane == 63) s_sum[wave] = inc;
+    __syncthreads();
+    unsigned long long above = inc - s;
+    for (int w = 0; w < wave; ++w) above += s_sum[w];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int c = kHistBins - 1 - (threadIdx.x * R + r);
+        if ((int64_t)above < S && (int64_t)(above + v[r]) >= S)  // exactly one bin
+            *cut = Cut{(uint32_t)c, c == kHistBins - 1 ? 1u : 0u, (int64_t)above};
+        above += v[r];
+    }
+}
+
+// Candidates counting at least c.
 __global__ __launch_bounds__(kThreads) void k_count_at_least(const uint32_t* __restrict__ cnt,
                                                              int64_t n, uint32_t c,
                                                              unsigned long long* __restrict__ out,
@@ -501,104 +626,88 @@ __global__ __launch_bounds__(kThreads) void k_count_at_least(const uint32_t* __r
     if ((threadIdx.x & 63) == 0 && m) atomicAdd(out, (unsigned long long)__popcll(m));
 }
 
-// Histogram of candidate counts, exact below kHistBins - 1 and pooled above:
-// a workgroup counts a run of candidates in LDS and adds its non-zero bins.
-constexpr int kHistBins = 4096;
-static_assert(kHistBins * sizeof(unsigned long long) >= kMaxBuckets * kGroups * sizeof(unsigned),
-              "the bucket sizes lie in the histogram's place");
-
-__global__ __launch_bounds__(kThreads) void k_count_hist(const uint32_t* __restrict__ cnt,
-                                                         int64_t n, int64_t per_block,
-                                                         unsigned long long* __restrict__ hist) {
-    __shared__ unsigned h[kHistBins];
-    for (int i = threadIdx.x; i < kHistBins; i += kThreads) h[i] = 0;
-    __syncthreads();
-    const int64_t i0 = (int64_t)blockIdx.x * per_block;
-    const int64_t i1 = i0 + per_block < n ? i0 + per_block : n;
-    for (int64_t i = i0 + threadIdx.x; i < i1; i += kThreads) {
-        const uint32_t c = cnt[i];
-        atomicAdd(&h[c < kHistBins - 1 ? c : kHistBins - 1], 1u);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < kHistBins; i += kThreads)
-        if (h[i]) atomicAdd(hist + i, (unsigned long long)h[i]);
-}
-
 struct LevelKeys {
     const uint64_t* skey[SCONE_MAX_FGRAM_LEN + 1];  // survivors' codes by scan
 };
 
-// Emit the selected candidates with their tokens.  A workgroup takes
-// kSelectPerBlock candidates and reserves its output rows with one atomic per
+// Emit the selected candidates with their tokens, unless the cut is still to
+// be found.  A workgroup takes kSelectPerBlock candidates at a time and reserves its output rows with one atomic per
 // counter (one per wavefront on a shared counter serialises).
 constexpr int kSelectPerBlock = 16 * kThreads;
 
 __global__ __launch_bounds__(kThreads) void k_select(
     const uint64_t* __restrict__ cand_key, const uint32_t* __restrict__ cand_count,
-    const int8_t* __restrict__ cand_level, int64_t n_cand, uint32_t thresh, int64_t n_above,
-    int64_t S, LevelKeys lk, int max_len, unsigned* __restrict__ n_gt,
+    const int8_t* __restrict__ cand_level, const unsigned* __restrict__ n_cands,
+    const Cut* __restrict__ cut, int64_t S, LevelKeys lk, int max_len, unsigned* __restrict__ n_gt,
     unsigned* __restrict__ n_eq, int32_t* __restrict__ fgrams, int32_t* __restrict__ lengths,
     int32_t* __restrict__ counts) {
     constexpr int R = kSelectPerBlock / kThreads;
     __shared__ unsigned s_gt, s_eq;
-    if (threadIdx.x == 0) s_gt = s_eq = 0;
-    const int64_t i0 = (int64_t)blockIdx.x * kSelectPerBlock + threadIdx.x;
+    if (cut->wide) return;
+    const uint32_t thresh = cut->thresh;
+    const int64_t n_above = cut->n_above, n_cand = *n_cands;
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (1ull << lane) - 1ull;
-    uint32_t c[R];
+    for (int64_t b0 = (int64_t)blockIdx.x * kSelectPerBlock; b0 < n_cand;
+         b0 += (int64_t)gridDim.x * kSelectPerBlock) {
+        const int64_t i0 = b0 + threadIdx.x;
+        if (threadIdx.x == 0) s_gt = s_eq = 0;
+        uint32_t c[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t i = i0 + r * kThreads;
-        c[r] = i < n_cand ? cand_count[i] : 0;  // a candidate counts at least 1
-    }
-    unsigned ng = 0, ne = 0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        ng += (unsigned)__popcll(__ballot(c[r] > thresh));
-        ne += (unsigned)__popcll(__ballot(c[r] && c[r] == thresh));
-    }
-    __syncthreads();
-    unsigned bg = 0, be = 0;
-    if (lane == 0) {
-        bg = atomicAdd(&s_gt, ng);
-        be = atomicAdd(&s_eq, ne);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        s_gt = s_gt ? atomicAdd(n_gt, s_gt) : 0;
-        s_eq = s_eq ? atomicAdd(n_eq, s_eq) : 0;
-    }
-    __syncthreads();
-    bg = (unsigned)__shfl((int)bg, 0) + s_gt;
-    be = (unsigned)__shfl((int)be, 0) + s_eq;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const bool gt = c[r] > thresh, eq = c[r] && c[r] == thresh;
-        const unsigned long long mg = __ballot(gt), me = __ballot(eq);
-        int64_t pos = -1;
-        if (gt) {
-            pos = bg + (unsigned)__popcll(mg & below);
-        } else if (eq) {
-            const int64_t e = (int64_t)be + (unsigned)__popcll(me & below);
-            if (n_above + e < S) pos = n_above + e;
+        for (int r = 0; r < R; ++r) {
+            const int64_t i = i0 + r * kThreads;
+            c[r] = i < n_cand ? cand_count[i] : 0;  // a candidate counts at least 1
         }
-        bg += (unsigned)__popcll(mg);
-        be += (unsigned)__popcll(me);
-        if (pos < 0 || pos >= S) continue;
-        const int64_t i = i0 + r * kThreads;
-        const int level = cand_level[i];
-        int32_t tok[SCONE_MAX_FGRAM_LEN];
-        uint64_t key = cand_key[i];
-        for (int L = level; L >= 3; --L) {
-            tok[L - 1] = (int32_t)(key & 0xFFFF);
-            key = lk.skey[L - 1][key >> 16];
+        unsigned ng = 0, ne = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            ng += (unsigned)__popcll(__ballot(c[r] > thresh));
+            ne += (unsigned)__popcll(__ballot(c[r] && c[r] == thresh));
         }
-        tok[1] = (int32_t)(key & 0xFFFF);
-        tok[0] = (int32_t)(key >> 16);
-        int32_t* row = fgrams + pos * (int64_t)max_len;
-        for (int j = 0; j < max_len; ++j) row[j] = j < level ? tok[j] : -1;
-        lengths[pos] = level;
-        counts[pos] = (int32_t)c[r];
+        __syncthreads();
+        unsigned bg = 0, be = 0;
+        if (lane == 0) {
+            bg = atomicAdd(&s_gt, ng);
+            be = atomicAdd(&s_eq, ne);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            s_gt = s_gt ? atomicAdd(n_gt, s_gt) : 0;
+            s_eq = s_eq ? atomicAdd(n_eq, s_eq) : 0;
+        }
+        __syncthreads();
+        bg = (unsigned)__shfl((int)bg, 0) + s_gt;
+        be = (unsigned)__shfl((int)be, 0) + s_eq;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool gt = c[r] > thresh, eq = c[r] && c[r] == thresh;
+            const unsigned long long mg = __ballot(gt), me = __ballot(eq);
+            int64_t pos = -1;
+            if (gt) {
+                pos = bg + (unsigned)__popcll(mg & below);
+            } else if (eq) {
+                const int64_t e = (int64_t)be + (unsigned)__popcll(me & below);
+                if (n_above + e < S) pos = n_above + e;
+            }
+            bg += (unsigned)__popcll(mg);
+            be += (unsigned)__popcll(me);
+            if (pos < 0 || pos >= S) continue;
+            const int64_t i = i0 + r * kThreads;
+            const int level = cand_level[i];
+            int32_t tok[SCONE_MAX_FGRAM_LEN];
+            uint64_t key = cand_key[i];
+            for (int L = level; L >= 3; --L) {
+                tok[L - 1] = (int32_t)(key & 0xFFFF);
+                key = lk.skey[L - 1][key >> 16];
+            }
+            tok[1] = (int32_t)(key & 0xFFFF);
+            tok[0] = (int32_t)(key >> 16);
+            int32_t* row = fgrams + pos * (int64_t)max_len;
+            for (int j = 0; j < max_len; ++j) row[j] = j < level ? tok[j] : -1;
+            lengths[pos] = level;
+            counts[pos] = (int32_t)c[r];
+        }
+        __syncthreads();  // the bases have been read
     }
 }
 
@@ -749,7 +858,9 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
         skeys[L] = reinterpret_cast<uint64_t*>(ws + lay.skey[L]);
         lk.skey[L] = skeys[L];
     }
-    // ctr: [0] status, [1] survivors, [2] candidates, [3] max count, [4] n_gt, [5] n_eq
+    // ctr: [0] status, [1] survivors, [2] candidates, [3] max count, [4] n_gt, [5] n_eq,
+    // [8..11] the cut
+    Cut* cut = reinterpret_cast<Cut*>(ctr + 8);
     int rc = SCONE_OK;
     const Shape sh = scan_shape(BT);
     const uint32_t n_tok = (uint32_t)BT, row = (uint32_t)T;
@@ -773,8 +884,9 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
         unsigned* cursors = starts + ((size_t)kGroups << sh.log2_buckets);
         hipLaunchKernelGGL(k_offsets, dim3(1), dim3(kMaxBuckets), 0, st, sizes,
                            1 << sh.log2_buckets, starts, cursors, ctr + 1);
-        hipLaunchKernelGGL(k_partition, dim3(sh.n_chunks), wide, 0, st, token_ids, n_tok, row, n,
-                           ids_prev, sh.chunk, sh.log2_buckets, cursors, items);
+        hipLaunchKernelGGL(n == 2 ? k_partition<true> : k_partition<false>, dim3(sh.n_chunks),
+                           wide, 0, st, token_ids, n_tok, row, ids_prev, sh.chunk,
+                           sh.log2_buckets, cursors, items);
         hipLaunchKernelGGL(k_bucket, dim3(1u << sh.log2_buckets), wide, 0, st, items, starts,
                            cursors, sh.log2_buckets, (uint32_t)min_count, n, n == 2 ? 1 : 0,
                            ctr + 1, n < max_len ? skeys[n] : nullptr, ctr + 2, cand_key,
@@ -783,88 +895,75 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
             hipLaunchKernelGGL(k_surv_clear, dim3(g_surv), narrow, 0, st, ctr + 1, table);
             hipLaunchKernelGGL(k_surv_insert, dim3(g_surv), narrow, 0, st, ctr + 1, skeys[n],
                                table);
-            hipLaunchKernelGGL(k_ids, dim3(g_pos), wide, 0, st, token_ids, n_tok, row, n, ids_prev,
-                               ctr + 1, table, sh.chunk, sh.n_chunks, sh.log2_buckets, ids_cur,
-                               sizes);
+            hipLaunchKernelGGL(n == 2 ? k_ids<true> : k_ids<false>, dim3(g_pos), wide, 0, st,
+                               token_ids, n_tok, row, ids_prev, ctr + 1, table, sh.chunk,
+                               sh.n_chunks, sh.log2_buckets, ids_cur, sizes);
             int32_t* tmp = ids_prev;
             ids_prev = ids_cur;
             ids_cur = tmp;
         }
         if (hipGetLastError() != hipSuccess) rc = SCONE_EHIP;
     }
-    unsigned h[4] = {0, 0, 0, 0};
-    if (rc == SCONE_OK &&
-        (hipMemcpyAsync(h, ctr, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess ||
-         hipStreamSynchronize(st) != hipSuccess))
-        rc = SCONE_EHIP;
+    // The cut and the selection follow without a look at the counters, unless
+    // the cut lies in the histogram's pooled bin.
+    const dim3 g_sel((unsigned)std::min<int64_t>((BT + kSelectPerBlock - 1) / kSelectPerBlock,
+                                                 2048));
+    auto select = [&]() {
+        hipLaunchKernelGGL(k_select, g_sel, narrow, 0, st, cand_key, cand_count, cand_level,
+                           ctr + 2, cut, S, lk, max_len, ctr + 4, ctr + 5, fgrams, lengths,
+                           counts);
+        return hipGetLastError() == hipSuccess;
+    };
+    unsigned h[16] = {};
+    static_assert(8 * sizeof(unsigned) + sizeof(Cut) <= sizeof(h), "the cut ends the counters");
+    auto read_counters = [&]() {
+        return hipMemcpyAsync(h, ctr, sizeof(h), hipMemcpyDeviceToHost, st) == hipSuccess &&
+               hipStreamSynchronize(st) == hipSuccess;
+    };
+    if (rc == SCONE_OK) {
+        if (hipMemsetAsync(hist, 0, kHistBins * sizeof(unsigned long long), st) != hipSuccess)
+            rc = SCONE_EHIP;
+        hipLaunchKernelGGL(k_count_hist,
+                           dim3((unsigned)std::min<int64_t>((BT + kHistRun - 1) / kHistRun, 1024)),
+                           narrow, 0, st, cand_count, ctr + 2, S, hist);
+        hipLaunchKernelGGL(k_cut, dim3(1), wide, 0, st, hist, ctr + 2, S, cut);
+        if (!select() || !read_counters()) rc = SCONE_EHIP;
+    }
     if (rc == SCONE_OK && h[0]) rc = SCONE_ETOKEN;
     const int64_t n_cand = h[2];
     const uint32_t max_c = h[3];
-    // Threshold: the largest count c with at least S candidates counting >= c.
-    auto at_least = [&](uint32_t c, int64_t& out) -> bool {
-        unsigned long long v = 0;
-        if (hipMemsetAsync(acc, 0, sizeof(v), st) != hipSuccess) return false;
-        if (launch_blocks((n_cand + kThreads - 1) / kThreads, kThreads,
-                          [&](int64_t b0, dim3 grid) {
-                              hipLaunchKernelGGL(k_count_at_least, grid, dim3(kThreads), 0, st,
-                                                 cand_count, n_cand, c, acc, b0);
-                          }) != hipSuccess ||
-            hipMemcpyAsync(&v, acc, sizeof(v), hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess)
-            return false;
-        out = (int64_t)v;
-        return true;
-    };
-    uint32_t thresh = 0;   // every candidate counts >= 1 > 0
-    int64_t n_above = 0;   // candidates counting > thresh
-    if (rc == SCONE_OK && n_cand > S) {
-        // One pass: a histogram of the counts, exact below kHistBins - 1.
-        std::vector<unsigned long long> hh(kHistBins, 0);
-        const int64_t per_block = 8192;
-        if (hipMemsetAsync(hist, 0, kHistBins * sizeof(unsigned long long), st) != hipSuccess)
-            rc = SCONE_EHIP;
-        if (rc == SCONE_OK) {
-            hipLaunchKernelGGL(k_count_hist, dim3((unsigned)((n_cand + per_block - 1) / per_block)),
-                               dim3(kThreads), 0, st, cand_count, n_cand, per_block, hist);
-            if (hipGetLastError() != hipSuccess ||
-                hipMemcpyAsync(hh.data(), hist, kHistBins * sizeof(unsigned long long),
-                               hipMemcpyDeviceToHost, st) != hipSuccess ||
+    Cut found{};
+    std::memcpy(&found, h + 8, sizeof(found));
+    if (rc == SCONE_OK && found.wide) {
+        // at least S candidates count >= kHistBins - 1: search the rest
+        auto at_least = [&](uint32_t c, int64_t& out) -> bool {
+            unsigned long long v = 0;
+            if (hipMemsetAsync(acc, 0, sizeof(v), st) != hipSuccess) return false;
+            if (launch_blocks((n_cand + kThreads - 1) / kThreads, kThreads,
+                              [&](int64_t b0, dim3 grid) {
+                                  hipLaunchKernelGGL(k_count_at_least, grid, dim3(kThreads), 0,
+                                                     st, cand_count, n_cand, c, acc, b0);
+                              }) != hipSuccess ||
+                hipMemcpyAsync(&v, acc, sizeof(v), hipMemcpyDeviceToHost, st) != hipSuccess ||
                 hipStreamSynchronize(st) != hipSuccess)
-                rc = SCONE_EHIP;
+                return false;
+            out = (int64_t)v;
+            return true;
+        };
+        uint32_t lo = kHistBins - 1, hi = max_c;  // at_least(lo) >= S
+        while (lo < hi && rc == SCONE_OK) {
+            const uint32_t mid = lo + (hi - lo + 1) / 2;
+            int64_t k = 0;
+            if (!at_least(mid, k)) rc = SCONE_EHIP;
+            else if (k >= S) lo = mid;
+            else hi = mid - 1;
         }
-        if (rc == SCONE_OK && (int64_t)hh[kHistBins - 1] < S) {
-            // the threshold is below the pooled bin: read it off the histogram
-            int64_t ge = (int64_t)hh[kHistBins - 1];  // candidates counting >= c + 1
-            for (uint32_t c = kHistBins - 2; c >= 1; --c) {
-                const int64_t ge_c = ge + (int64_t)hh[c];
-                if (ge_c >= S) {
-                    thresh = c;
-                    n_above = ge;
-                    break;
-                }
-                ge = ge_c;
-            }
-        } else if (rc == SCONE_OK) {
-            // at least S candidates count >= kHistBins - 1: search the rest
-            uint32_t lo = kHistBins - 1, hi = max_c;  // at_least(lo) >= S
-            while (lo < hi && rc == SCONE_OK) {
-                const uint32_t mid = lo + (hi - lo + 1) / 2;
-                int64_t k = 0;
-                if (!at_least(mid, k)) rc = SCONE_EHIP;
-                else if (k >= S) lo = mid;
-                else hi = mid - 1;
-            }
-            thresh = lo;
-            if (rc == SCONE_OK && thresh < max_c && !at_least(thresh + 1, n_above))
-                rc = SCONE_EHIP;
-        }
-    }
-    if (rc == SCONE_OK && n_cand > 0) {
-        hipLaunchKernelGGL(k_select,
-                           dim3((unsigned)((n_cand + kSelectPerBlock - 1) / kSelectPerBlock)),
-                           narrow, 0, st, cand_key, cand_count, cand_level, n_cand, thresh,
-                           n_above, S, lk, max_len, ctr + 4, ctr + 5, fgrams, lengths, counts);
-        if (hipGetLastError() != hipSuccess) rc = SCONE_EHIP;
+        found = Cut{lo, 0, 0};
+        if (rc == SCONE_OK && lo < max_c && !at_least(lo + 1, found.n_above)) rc = SCONE_EHIP;
+        if (rc == SCONE_OK &&
+            (hipMemcpyAsync(cut, &found, sizeof(found), hipMemcpyHostToDevice, st) != hipSuccess ||
+             !select()))
+            rc = SCONE_EHIP;
     }
     release();
     if (rc == SCONE_OK) *n_found = n_cand < S ? n_cand : S;
