@@ -1,5 +1,5 @@
 """Rows of any width and alignment through the copies that move them in 16-byte
-units (gather, embed, the pipelined step): edges of the units, of a workgroup's
+units (gather, embed, the pipelined step, decode): edges of the units, of a workgroup's
 1,024 units and of the row, unaligned tables and outputs, ids out of range."""
 import numpy as np
 import pytest
@@ -53,6 +53,16 @@ def test_widths_and_alignments(row_bytes, at):
         assert np.array_equal(out.cpu().numpy(), want), call
         edge = torch.cat([hold[:at[1]], hold[at[1] + size:]]).cpu().numpy()
         assert (edge == 0xA5).all(), call
+    # a decoding step with the row's second-to-last token as context
+    size = 3 * row_bytes
+    hold = torch.full((size + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    out = hold[at[1]:at[1] + size].view(3, row_bytes)
+    ctx, one = dev(X[:, -2:-1].copy()), torch.ones(3, dtype=torch.int32, device="cuda")
+    S.decode_step(table, ctx, one, dev(X[:, -1].copy()), 2, rows, out)
+    assert S.check() == (S.scone.EROW if bad[:, -1].any() else S.scone.OK)
+    assert np.array_equal(out.cpu().numpy(), want[:, -1])
+    edge = torch.cat([hold[:at[1]], hold[at[1] + size:]]).cpu().numpy()
+    assert (edge == 0xA5).all()
 
 
 def test_rows_past_2_gib():
