@@ -117,6 +117,26 @@ constexpr int kWaitLds = 0xF | (7 << 4) | (0 << 8) | (3 << 14);
 constexpr int kBK = 64;        // k-slab depth (elements)
 constexpr int kRowBytes = 128;  // one slab row in LDS
 
+// Consecutive workgroups land on different XCDs; renumber so that each XCD walks
+// a contiguous run of tiles, and order that run in groups of kGroupM tile rows, m
+// fastest inside a group, so that the workgroups an XCD runs at once share A and
+// W slabs in its L2: 32 of them as 8 rows by 4 columns touch 12 slabs per k-step,
+// where a run along n touches 15 on a 12-column product and 18 on a 16-column one
+// (4-column products were 8 by 4 already).
+struct TileAt {
+    int m, n;
+};
+__device__ __forceinline__ TileAt tile_at(int b, int nb, int tiles_m, int tiles_n) {
+    constexpr int kGroupM = 8;
+    const int per = nb / 8;
+    const int t = (b < per * 8) ? (b % 8) * per + b / 8 : b;
+    const int group = t / (kGroupM * tiles_n);
+    const int first = group * kGroupM;
+    const int gm = tiles_m - first < kGroupM ? tiles_m - first : kGroupM;
+    const int tr = t - group * kGroupM * tiles_n;
+    return {first + tr % gm, tr / gm};
+}
+
 template <int EPI, int BM, int BN, int WGM, int WGN, bool kStaged>
 __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(const uint16_t* __restrict__ A,
                                                          const uint16_t* __restrict__ W,
@@ -134,25 +154,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(const uint16_t* __restr
     constexpr int SMEM = kStaged && NW * WTM * ERS > 2 * STAGE ? NW * WTM * ERS : 2 * STAGE;
     __shared__ __attribute__((aligned(1024))) uint8_t smem[SMEM];
 
-    // Consecutive workgroups land on different XCDs; renumber so that each
-    // XCD walks a contiguous run of tiles, and order that run in groups of
-    // kGroupM tile rows, m fastest inside a group, so that the workgroups an
-    // XCD runs at once share A and W slabs in its L2: 32 of them as 8 rows by
-    // 4 columns touch 12 slabs per k-step, where a run along n touches 15 on
-    // a 12-column product and 18 on a 16-column one (4-column products were
-    // 8 by 4 already).
-    constexpr int kGroupM = 8;
-    const int nb = gridDim.x;
-    const int b = blockIdx.x;
-    const int per = nb / 8;
-    const int t = (b < per * 8) ? (b % 8) * per + b / 8 : b;
-    const int tiles_m = (M + BM - 1) / BM;
-    const int group = t / (kGroupM * tiles_n);
-    const int first = group * kGroupM;
-    const int gm = tiles_m - first < kGroupM ? tiles_m - first : kGroupM;
-    const int tr = t - group * kGroupM * tiles_n;
-    const int tm = first + tr % gm, tn = tr / gm;
-    const int m0 = tm * BM, n0 = tn * BN;
+    const TileAt tile = tile_at(blockIdx.x, gridDim.x, (M + BM - 1) / BM, tiles_n);
+    const int m0 = tile.m * BM, n0 = tile.n * BN;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -398,6 +401,208 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(const uint16_t* __restr
     }
 }
 
+// out += A W^T + bias on 256 x (128 + 64 X1) tiles, eight wavefronts in two groups
+// of four that run one phase apart: while one group multiplies, the other reads
+// its next fragments and starts copies.  A slab is four phases, the quadrants of
+// the tile by halves of A (64 rows of each per wavefront) and parts of W (128 and
+// 64 X1 columns, 32 and 16 X1 per wavefront); quadrants (0,0), (0,1), (1,1), (1,0)
+// load W0 and A0, W1, A1, nothing.  A part of the ring is refilled as soon as the
+// barrier after its last read: A1 of slab t + 1 in the first phase, W0, A0 and W1
+// of slab t + 2 in the others, so that the one counted wait of a slab leaves those
+// three in flight.
+//
+// The main loop runs as fast as k_gemm's (1,463 against 1,479 TFLOP/s at M = N = K =
+// 8,192); it is here because its accumulators and fragments leave registers for the
+// residual values, whose loads are in flight two quadrants ahead, and because a
+// width of 192 fills the chip where 256 does not: 65,459 x 1,024 x 4,096 492 -> 479
+// us, 6,800 x 1,536 x 6,144 156 (128 x 128 tiles) -> 128 us, x 1,536 52 -> 46 us.
+template <int X1>
+__global__ __launch_bounds__(512) void k_gemm_resid(const uint16_t* __restrict__ A,
+                                                    const uint16_t* __restrict__ W,
+                                                    const uint16_t* __restrict__ bias,
+                                                    float* __restrict__ out, int64_t ldc, int M,
+                                                    int K, int tiles_n) {
+    constexpr int kHalf = 128 * kRowBytes;                   // 128 rows of a slab
+    constexpr int kStage = 3 * kHalf + X1 * 64 * kRowBytes;  // A0 A1 W0 W1
+    constexpr int kBN = 128 + 64 * X1;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * kStage];
+
+    const TileAt tile = tile_at(blockIdx.x, gridDim.x, (M + 255) / 256, tiles_n);
+    const int m0 = tile.m * 256, n0 = tile.n * kBN;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 2, wn = wave & 3;  // wm is the group
+
+    // Copies: a wavefront fills 16 rows of A0, A1 and W0 and 8 X1 of W1, 8 rows per
+    // instruction; lane l covers row l / 8 and slot l % 8 (as in k_gemm).
+    const int lrow = lane >> 3, lslot = lane & 7;
+    const uint32_t voff = (uint32_t)(lrow * K + (lslot ^ lrow) * 8) * 2;
+    const int64_t row8 = (int64_t)K * 16;  // bytes of 8 rows
+    const uint8_t* part[4];
+    part[0] = reinterpret_cast<const uint8_t*>(A + (int64_t)(m0 + wave * 16) * K);
+    part[1] = part[0] + 16 * row8;
+    part[2] = reinterpret_cast<const uint8_t*>(W + (int64_t)(n0 + wave * 16) * K);
+    part[3] = reinterpret_cast<const uint8_t*>(W + (int64_t)(n0 + 128 + wave * 8 * X1) * K);
+    enum { kA0, kA1, kW0, kW1 };
+    auto issue = [&](int what, int slab) {
+        const uint8_t* g = part[what] + (int64_t)slab * (kBK * 2) + voff;
+        uint8_t* d = smem + (slab & 1) * kStage + what * kHalf +
+                     wave * (what == kW1 ? 1024 * X1 : 2048);
+        __builtin_amdgcn_global_load_lds((gbl_ptr_t)g, (lds_ptr_t)d, 16, 0, 0);
+        if (what == kW1 && X1 == 1) return;
+        __builtin_amdgcn_global_load_lds((gbl_ptr_t)(g + row8), (lds_ptr_t)(d + 1024), 16, 0, 0);
+    };
+
+    f32x4 acc[2][2][2][4];  // [A half][W part][16 columns][16 rows]
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 4; ++y) acc[i][j][x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const int fr = lane & 15, q0 = lane >> 4;
+    const int slot[2] = {(q0 ^ (lane & 7)) * 16, ((4 + q0) ^ (lane & 7)) * 16};
+    bf16x8 fa[4][2], fw0[2][2], fw1[X1][2];  // [16 rows or columns][half slab]
+    // Fragments of 16 * rows of one part from row `first` on.
+    auto read = [&](int stage, int what, int first, auto& f) {
+        constexpr int kRows = sizeof(f) / sizeof(f[0]);
+        const uint8_t* p = smem + stage * kStage + what * kHalf + (first + fr) * kRowBytes;
+#pragma unroll
+        for (int y = 0; y < kRows; ++y)
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                f[y][k] = __builtin_bit_cast(
+                    bf16x8, *reinterpret_cast<const u32x4*>(p + y * 16 * kRowBytes + slot[k]));
+    };
+    auto multiply = [&](f32x4 (&c)[2][4], const auto& f) {
+        constexpr int kCols = sizeof(f) / sizeof(f[0]);
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int x = 0; x < kCols; ++x)
+#pragma unroll
+                for (int y = 0; y < 4; ++y)
+                    c[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[x][k], fa[y][k], c[x][y],
+                                                                      0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+    };
+    auto barrier = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto settle = [&]() {  // this wavefront's fragments are in registers
+        __builtin_amdgcn_s_waitcnt(kWaitLds);
+        barrier();
+    };
+    const int KT = K / kBK;
+    issue(kW0, 0);
+    issue(kA0, 0);
+    issue(kW1, 0);
+    issue(kA1, 0);
+    if (KT > 1) {
+        issue(kW0, 1);
+        issue(kA0, 1);
+        issue(kW1, 1);
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(4 + X1));
+    } else {
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    }
+    barrier();
+    if (wm == 1) barrier();  // the second group starts a phase later
+    // Slab t; kMore: how many follow it, 2 for more than one.
+    auto step = [&](int t, auto more_c) {
+        constexpr int kMore = decltype(more_c)::value;
+        const int st = t & 1;
+        read(st, kW0, wn * 32, fw0);
+        read(st, kA0, wm * 64, fa);
+        if constexpr (kMore >= 1) issue(kA1, t + 1);
+        settle();
+        multiply(acc[0][0], fw0);
+        barrier();
+        read(st, kW1, wn * 16 * X1, fw1);
+        if constexpr (kMore >= 2) issue(kW0, t + 2);
+        settle();
+        multiply(acc[0][1], fw1);
+        barrier();
+        read(st, kA1, wm * 64, fa);
+        if constexpr (kMore >= 2) issue(kA0, t + 2);
+        settle();
+        multiply(acc[1][1], fw1);
+        barrier();
+        // Slab t + 1 has landed when only the copies of slab t + 2 are left; the
+        // other group's wait for its copies lies a phase later, still before
+        // either group's first read of the slab.
+        if constexpr (kMore >= 2) {
+            issue(kW1, t + 2);
+            __builtin_amdgcn_s_waitcnt(waitcnt_vm(4 + X1));
+        } else if constexpr (kMore == 1) {
+            __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+        }
+        barrier();
+        multiply(acc[1][0], fw0);
+        barrier();
+    };
+    int kt = 0;
+    for (; kt + 2 < KT; ++kt) step(kt, std::integral_constant<int, 2>{});
+    if (kt + 1 < KT) step(kt++, std::integral_constant<int, 1>{});
+    step(kt, std::integral_constant<int, 0>{});
+    if (wm == 0) barrier();
+
+    // acc[i][j][x][y][r] = C[m, n], n the column of lane / 16 and r, m the row of
+    // lane % 16; rows past M read row M - 1 and are not stored.
+    const int er = lane & 15, ec = (lane >> 4) * 4;
+    f32x4 h[4][2][4];  // residual values by quadrant
+    auto load = [&](int q) {
+        const int n = n0 + ((q & 1) ? 128 + wn * 16 * X1 : wn * 32) + ec;
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            const int m = m0 + (q >> 1) * 128 + wm * 64 + y * 16 + er;
+            const float* p = out + (int64_t)(m < M ? m : M - 1) * ldc + n;
+#pragma unroll
+            for (int x = 0; x < ((q & 1) ? X1 : 2); ++x)
+                h[q][x][y] = *reinterpret_cast<const f32x4*>(p + x * 16);
+        }
+    };
+    load(0);
+    load(1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (q < 2) load(q + 2);
+        const int i = q >> 1, j = q & 1;
+#pragma unroll
+        for (int x = 0; x < (j ? X1 : 2); ++x) {
+            const int n = n0 + (j ? 128 + wn * 16 * X1 : wn * 32) + x * 16 + ec;
+            const u32x2 bb = *reinterpret_cast<const u32x2*>(bias + n);
+            const float b0 = bf16_to_f32(bb.x & 0xFFFFu), b1 = bf16_to_f32(bb.x >> 16);
+            const float b2 = bf16_to_f32(bb.y & 0xFFFFu), b3 = bf16_to_f32(bb.y >> 16);
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                const int m = m0 + i * 128 + wm * 64 + y * 16 + er;
+                f32x4 v = h[q][x][y];
+                v[0] += acc[i][j][x][y][0] + b0;
+                v[1] += acc[i][j][x][y][1] + b1;
+                v[2] += acc[i][j][x][y][2] + b2;
+                v[3] += acc[i][j][x][y][3] + b3;
+                if (m < M) *reinterpret_cast<f32x4*>(out + (int64_t)m * ldc + n) = v;
+            }
+        }
+    }
+}
+
+template <int X1>
+inline hipError_t launch_resid(const uint16_t* A, const uint16_t* W, const uint16_t* bias,
+                               void* out, int64_t ldc, int M, int N, int K, hipStream_t st) {
+    const int tiles_n = N / (128 + 64 * X1), tiles_m = (M + 255) / 256;
+    hipLaunchKernelGGL(k_gemm_resid<X1>, dim3((unsigned)(tiles_m * tiles_n)), dim3(512), 0, st, A,
+                       W, bias, static_cast<float*>(out), ldc, M, K, tiles_n);
+    return hipGetLastError();
+}
+
 template <int EPI, int BM, int BN, int WGM, int WGN>
 inline hipError_t launch_tiles(const uint16_t* A, const uint16_t* W, const uint16_t* bias,
                                void* out, int64_t ldc, int M, int N, int K, hipStream_t st) {
@@ -422,11 +627,29 @@ inline hipError_t launch_tiles(const uint16_t* A, const uint16_t* W, const uint1
 // take 128 x 128 on four.  The eight wavefronts of a 256 x 256 tile own
 // 64 x 128 parts (four down, two across): measured faster than 128 x 64
 // parts on every product of the f-gram model.
+//
+// The residual product takes the tile with the least rounds times the length of
+// one: a round of 256 x 192 tiles is 0.78 of one of 256 x 256, and one of 128 x 128
+// tiles, two per compute unit, 0.61 (6,800 and 3,001 rows, N = 1,536, K = 6,144:
+// 142, 109 and 87 us).
 template <int EPI>
 inline hipError_t launch(const uint16_t* A, const uint16_t* W, const uint16_t* bias, void* out,
                          int64_t ldc, int M, int N, int K, hipStream_t st) {
-    if (N % 256 == 0 && (int64_t)((M + 255) / 256) * (N / 256) >= 256)
-        return launch_tiles<EPI, 256, 256, 4, 2>(A, W, bias, out, ldc, M, N, K, st);
+    if constexpr (EPI == kResid) {
+        auto rounds = [&](int bm, int bn, int at_once) {
+            const int64_t tiles = (int64_t)((M + bm - 1) / bm) * (N / bn);
+            return (tiles + at_once - 1) / at_once;
+        };
+        const int64_t c128 = 61 * rounds(128, 128, 512);
+        const int64_t c192 = N % 192 == 0 ? 78 * rounds(256, 192, 256) : INT64_MAX;
+        const int64_t c256 = N % 256 == 0 ? 100 * rounds(256, 256, 256) : INT64_MAX;
+        if (c256 < c128 && c256 <= c192)
+            return launch_resid<2>(A, W, bias, out, ldc, M, N, K, st);
+        if (c192 < c128) return launch_resid<1>(A, W, bias, out, ldc, M, N, K, st);
+    } else {
+        if (N % 256 == 0 && (int64_t)((M + 255) / 256) * (N / 256) >= 256)
+            return launch_tiles<EPI, 256, 256, 4, 2>(A, W, bias, out, ldc, M, N, K, st);
+    }
     return launch_tiles<EPI, 128, 128, 2, 2>(A, W, bias, out, ldc, M, N, K, st);
 }
 
