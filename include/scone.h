@@ -382,9 +382,9 @@ int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_t T, int32_
                           int64_t workspace_bytes, void* stream);
 
 /* Bytes of workspace scone_discover_fgrams needs for a [B, T] corpus and
- * f-grams up to max_len tokens (a counting table of 16-byte slots, at least
- * 2 B T of them, plus about (13 (max_len - 1) + 8 (max_len - 2) + 8) B T
- * bytes of per-scan arrays), or -1 for sizes the call rejects. */
+ * f-grams up to max_len tokens (room for a table of 16-byte slots, at least
+ * 2 B T of them, where a scan's items lie first, plus about
+ * (13 (max_len - 1) + 8 (max_len - 2) + 8) B T bytes of per-scan arrays), or -1 for sizes the call rejects. */
 int64_t scone_discover_workspace(int64_t B, int64_t T, int32_t max_len);
 
 /*
