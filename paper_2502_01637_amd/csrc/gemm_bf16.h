@@ -629,20 +629,22 @@ inline hipError_t launch_tiles(const uint16_t* A, const uint16_t* W, const uint1
 // parts on every product of the f-gram model.
 //
 // The residual product takes the tile with the least rounds times the length of
-// one: a round of 256 x 192 tiles is 0.78 of one of 256 x 256, and one of 128 x 128
-// tiles, two per compute unit, 0.61 (6,800 and 3,001 rows, N = 1,536, K = 6,144:
-// 142, 109 and 87 us).
+// one, in hundredths of a round of 256 x 256 tiles with a long sum: 116 with K up to
+// 1,024, 78 for 256 x 192, 70 for 128 x 128, two per compute unit, and 45 for their
+// last round where one per unit is enough.  Over 96 shapes (N 512 to 2,048, K = N and
+// 4 N, 700 to 30,000 rows) the choice is within 0.5% of the best on average and 10%
+// at most (6,800, 3,001 and 20,000 rows, N = 1,536, 1,536 and 1,024, K = 4 N: 256 x
+// 256 142, 122 and 200 us, 256 x 192 109, 110 us, 128 x 128 156, 87 and 179 us).
 template <int EPI>
 inline hipError_t launch(const uint16_t* A, const uint16_t* W, const uint16_t* bias, void* out,
                          int64_t ldc, int M, int N, int K, hipStream_t st) {
     if constexpr (EPI == kResid) {
-        auto rounds = [&](int bm, int bn, int at_once) {
-            const int64_t tiles = (int64_t)((M + bm - 1) / bm) * (N / bn);
-            return (tiles + at_once - 1) / at_once;
-        };
-        const int64_t c128 = 61 * rounds(128, 128, 512);
-        const int64_t c192 = N % 192 == 0 ? 78 * rounds(256, 192, 256) : INT64_MAX;
-        const int64_t c256 = N % 256 == 0 ? 100 * rounds(256, 256, 256) : INT64_MAX;
+        auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * (N / bn); };
+        auto rounds = [&](int bn) { return (tiles(256, bn) + 255) / 256; };
+        const int64_t t128 = tiles(128, 128), rest = t128 % 512;
+        const int64_t c128 = 70 * (t128 / 512) + (rest > 256 ? 70 : rest > 0 ? 45 : 0);
+        const int64_t c192 = N % 192 == 0 ? 78 * rounds(192) : INT64_MAX;
+        const int64_t c256 = N % 256 == 0 ? (K <= 1024 ? 116 : 100) * rounds(256) : INT64_MAX;
         if (c256 < c128 && c256 <= c192)
             return launch_resid<2>(A, W, bias, out, ldc, M, N, K, st);
         if (c192 < c128) return launch_resid<1>(A, W, bias, out, ldc, M, N, K, st);

@@ -18,8 +18,8 @@ pytestmark = pytest.mark.gpu
 # (d_ff = 128, two slabs) and an odd number of slabs.
 @pytest.mark.parametrize("d,heads,ff,n", [
     (1536, 12, 128, 5376), (1536, 12, 128, 5377), (1536, 12, 1152, 6913),
-    (1536, 12, 384, 8192), (1536, 12, 256, 8193), (512, 8, 128, 16_385),
-    (1024, 8, 640, 16_500)])
+    (1536, 12, 384, 8192), (1536, 12, 256, 8193), (512, 8, 128, 32_700),
+    (1024, 8, 640, 16_300)])
 def test_tile_choice(d, heads, ff, n):
     cfg = ModelConfig(d, heads, ff, 1, 3)
     rng = np.random.default_rng(n)
