@@ -632,7 +632,7 @@ inline hipError_t launch_tiles(const uint16_t* A, const uint16_t* W, const uint1
 // one, in hundredths of a round of 256 x 256 tiles with a long sum: 116 with K up to
 // 1,024, 78 for 256 x 192, 70 for 128 x 128, two per compute unit, and 45 for their
 // last round where one per unit is enough.  Over 96 shapes (N 512 to 2,048, K = N and
-// 4 N, 700 to 30,000 rows) the choice is within 0.5% of the best on average and 10%
+// 4 N, 700 to 30,000 rows) the choice is within 0.3% of the best on average and 10%
 // at most (6,800, 3,001 and 20,000 rows, N = 1,536, 1,536 and 1,024, K = 4 N: 256 x
 // 256 142, 122 and 200 us, 256 x 192 109, 110 us, 128 x 128 156, 87 and 179 us).
 template <int EPI>
