@@ -3,7 +3,7 @@
 //
 //   C[m, n] = sum_k A[m, k] * W[n, k] + bias[n]        (A [M, K], W [N, K])
 //   kBias:  out_bf16[m, n]  = bf16(C)
-//   kGelu:  out_bf16[m, n]  = bf16(GELU(C))             (erf form)
+//   kGelu:  out_bf16[m, n]  = bf16(GELU(C))             (x Phi(x), not the tanh form)
 //   kResid: out_f32[m, n]  += C                         (the residual stream)
 //
 // Both operands are K-contiguous.  A workgroup computes a BM x BN tile over
@@ -80,8 +80,9 @@ __device__ __forceinline__ uint32_t f32_to_bf16(float f) {
 // is 2.5e-7 and the rms over a standard normal 3.1e-8, where Abramowitz and
 // Stegun's 7.1.26 erf gave 4.7e-7 and 5.7e-8 with a reciprocal more and six more
 // VALU instructions: the epilogue of a 256 x 256 tile is bound by them (each lane
-// evaluates 128); the product inside the precompute of 1M f-grams 565 -> 517 us.  The
-// maximum passes NaN on.
+// evaluates 128); the product inside the precompute of 1M f-grams 565 -> 517 us.
+// max(x, 0) is taken as x / 2 + |x| / 2, exact for every finite x, so that NaN
+// passes on and -inf gives NaN as the erf form does (-inf times 0).
 __device__ __forceinline__ float gelu_erf(float x) {
     const float z = __builtin_amdgcn_fmed3f(__builtin_fabsf(x), 0.0f, 7.0f);
     float p = 1.01424612e-07f;
@@ -94,7 +95,8 @@ __device__ __forceinline__ float gelu_erf(float x) {
     p = p * z - 0.459162301f;
     p = p * z - 1.15111041f;
     p = p * z - 0.999999899f;
-    return __builtin_elementwise_maximum(x, 0.0f) - z * __builtin_amdgcn_exp2f(p);
+    const float pos = __builtin_fmaf(0.5f, __builtin_fabsf(x), 0.5f * x);
+    return pos - z * __builtin_amdgcn_exp2f(p);
 }
 
 // The lane id, computed from the execution mask with an operand the

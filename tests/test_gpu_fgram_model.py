@@ -300,3 +300,23 @@ def test_random_model_shapes(case):
                       {k: bf16_bits_to_f64(v) for k, v in P.items()}, layers, d // dh)
     assert_close(got[row_ids[sample]], ref, layers, f"case {case}")
     assert not got[[0, 1, 2]].any()
+
+
+@pytest.mark.parametrize("d_ff,N", [(512, 300), (2048, 8200)])
+def test_infinite_preactivations(d_ff, N):
+    """A GELU input of -inf is NaN (-inf times 0) as in the oracle, one of +inf
+    stays infinite; the other products' tiles, small and large."""
+    cfg = ModelConfig(512, 8, d_ff, 1, 2)
+    rng = np.random.default_rng(3)
+    T = make_token_rows(300, cfg.d, seed=2)
+    fg, lengths = random_fgrams(rng, 300, N, 2)
+    ids = np.arange(N, dtype=np.int32)
+    for value in (-np.inf, np.inf, np.nan, -1e38):
+        P = make_params(cfg, seed=1)
+        P["l0.b_fc1"][5] = np.float32(value).view(np.uint32) >> 16
+        got = as_f64(run(cfg, fg, lengths, ids, T, P, N))
+        with np.errstate(all="ignore"):
+            ref = orc.forward(fg[:20], lengths[:20], bf16_bits_to_f64(T),
+                              {k: bf16_bits_to_f64(v) for k, v in P.items()}, 1, 8)
+        assert np.array_equal(np.isnan(got[:20]), np.isnan(ref)), value
+        assert np.isnan(got).all() == np.isnan(ref).all() == (value != -1e38), value
