@@ -631,19 +631,21 @@ struct LevelKeys {
 };
 
 // Emit the selected candidates with their tokens, unless the cut is still to
-// be found.  A workgroup takes kSelectPerBlock candidates at a time and reserves its output rows with one atomic per
-// counter (one per wavefront on a shared counter serialises).
+// be found or the corpus was rejected (an error leaves the outputs as they were).
+// A workgroup takes kSelectPerBlock candidates at a time and reserves its output
+// rows with one atomic per counter (one per wavefront on a shared counter
+// serialises).
 constexpr int kSelectPerBlock = 16 * kThreads;
 
 __global__ __launch_bounds__(kThreads) void k_select(
     const uint64_t* __restrict__ cand_key, const uint32_t* __restrict__ cand_count,
     const int8_t* __restrict__ cand_level, const unsigned* __restrict__ n_cands,
-    const Cut* __restrict__ cut, int64_t S, LevelKeys lk, int max_len, unsigned* __restrict__ n_gt,
+    const unsigned* __restrict__ status, const Cut* __restrict__ cut, int64_t S, LevelKeys lk, int max_len, unsigned* __restrict__ n_gt,
     unsigned* __restrict__ n_eq, int32_t* __restrict__ fgrams, int32_t* __restrict__ lengths,
     int32_t* __restrict__ counts) {
     constexpr int R = kSelectPerBlock / kThreads;
     __shared__ unsigned s_gt, s_eq;
-    if (cut->wide) return;
+    if (cut->wide || *status) return;
     const uint32_t thresh = cut->thresh;
     const int64_t n_above = cut->n_above, n_cand = *n_cands;
     const int lane = threadIdx.x & 63;
@@ -910,7 +912,7 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
                                                  2048));
     auto select = [&]() {
         hipLaunchKernelGGL(k_select, g_sel, narrow, 0, st, cand_key, cand_count, cand_level,
-                           ctr + 2, cut, S, lk, max_len, ctr + 4, ctr + 5, fgrams, lengths,
+                           ctr + 2, ctr + 0, cut, S, lk, max_len, ctr + 4, ctr + 5, fgrams, lengths,
                            counts);
         return hipGetLastError() == hipSuccess;
     };

@@ -2,6 +2,8 @@
 (small corpora) and against torch.unique (corpora too large for it): one
 bucket and many, chunks of every length, remainders, buckets with more codes
 than one LDS table holds, one n-gram at every position."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -90,3 +92,21 @@ def test_buckets_with_more_codes_than_a_table():
 def test_one_ngram_everywhere(B, T):
     X = torch.full((B, T), 65_535, device="cuda", dtype=torch.int32)
     check_all(X, 6 if T > 6 else 2, 1)
+
+
+@pytest.mark.parametrize("where", [0, 1, 4999, 123_456])
+def test_rejected_corpus_leaves_the_outputs(where):
+    """A token out of range: an error, and the outputs as they were."""
+    B, T, K, Sn = 50, 5000, 4, 1000
+    g = torch.Generator(device="cuda").manual_seed(2)
+    X = torch.randint(0, 900, (B, T), device="cuda", generator=g, dtype=torch.int32)
+    X.view(-1)[where] = 65_536 if where % 2 else -1
+    fg = torch.full((Sn, K), -77, dtype=torch.int32, device="cuda")
+    ln, ct = fg[:, 0].clone(), fg[:, 0].clone()
+    n = ctypes.c_int64(5)
+    rc = S.scone.lib().scone_discover_fgrams(
+        X.data_ptr(), B, T, K, 1, Sn, fg.data_ptr(), ln.data_ptr(), ct.data_ptr(),
+        ctypes.byref(n), None, 0, torch.cuda.current_stream().cuda_stream)
+    assert rc == S.scone.ETOKEN and n.value == 0
+    for t in (fg, ln, ct):
+        assert (t == -77).all()
