@@ -22,6 +22,8 @@
 //                previous pass over the positions counted (an upper bound)
 //   k_partition  a workgroup merges equal codes of its chunk in LDS and writes
 //                one 8-byte item (code, count) per distinct code to its bucket
+//   k_sub_*      corpora above kSplitFrom positions: every bucket split once more
+//   k_split      by the hash's next bits, so that the parts fit LDS at any size
 //   k_bucket     one workgroup per bucket: counts in LDS, then the survivors'
 //                dense ids and the candidates, in runs
 //   k_surv_*     a hash table of the survivors alone (code -> dense id)
@@ -76,6 +78,15 @@ __device__ __forceinline__ uint32_t bucket_of(uint64_t h, int log2_buckets) {
 }
 __device__ __forceinline__ uint64_t part_of(uint64_t h, int log2_buckets, int bits) {
     return ((h << log2_buckets) >> 1) >> (63 - bits);
+}
+
+// __syncthreads after this wavefront's LDS operations have completed.  The
+// barrier alone is meant to do that, but in k_ids the compiler (ROCm 7.2)
+// leaves the wait out on the paths from the counting adds to it, and a
+// wavefront's counts were then missing from the sums now and then.
+__device__ __forceinline__ void lds_settled_barrier() {
+    __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
+    __syncthreads();
 }
 
 // Code of the 2-gram ending at flat position i, or kEmptyKey.  (Every load of
@@ -166,8 +177,68 @@ __global__ __launch_bounds__(kMaxBuckets) void k_offsets(unsigned* __restrict__ 
             sizes[b * kGroups + g] = 0;
             at += v[g];
         }
+        if (b == buckets - 1) starts[buckets * kGroups] = at;  // the end mark
     }
     if (b == 0) *n_surv = 0;
+}
+
+// The LDS of a workgroup that partitions up to kMaxChunk items.
+struct PartLds {
+    unsigned long long item[kMaxChunk];
+    unsigned hist[kMaxBuckets], region[kMaxBuckets], wave[kWide / 64];
+};
+
+// Writes a workgroup's items (0 for none, at most kMaxChunk of them) to the
+// regions of their bins (at most kMaxBuckets): bin b's next free place is
+// cursors[b * stride].  Every thread calls it, with l.hist zero and l.item free.
+template <int N, typename BinOf>
+__device__ __forceinline__ void write_by_bin(const uint64_t (&item)[N], int bins, BinOf bin_of,
+                                             unsigned* __restrict__ cursors, int stride,
+                                             uint64_t* __restrict__ out, PartLds& l) {
+    static_assert(kMaxBuckets == kWide, "a thread per bin");
+    // Every item's bin and its rank among the workgroup's items there.
+    unsigned at[N];
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        if (!item[r]) continue;
+        const uint32_t b = bin_of(item[r]);
+        at[r] = b << 16 | atomicAdd(&l.hist[b], 1u);
+    }
+    __syncthreads();
+    // A thread per bin: where its items start, in LDS and in its region.
+    const int b = threadIdx.x, lane = b & 63;
+    const unsigned mine = b < bins ? l.hist[b] : 0;
+    unsigned inc = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned y = (unsigned)__shfl_up((int)inc, o);
+        if (lane >= o) inc += y;
+    }
+    if (lane == 63) l.wave[b >> 6] = inc;
+    const unsigned region = mine ? atomicAdd(cursors + b * stride, mine) : 0;
+    __syncthreads();
+    unsigned start = inc - mine, total = 0;
+    for (int w = 0; w < kWide / 64; ++w) {
+        if (w < b >> 6) start += l.wave[w];
+        total += l.wave[w];
+    }
+    l.hist[b] = start;
+    l.region[b] = region - start;
+    __syncthreads();
+    // The items by bin in LDS, so that neighbouring lanes write neighbouring
+    // items: one store transaction per run where one per item (8 bytes at 64
+    // places per wavefront) ran at the rate of random accesses.
+#pragma unroll
+    for (int r = 0; r < N; ++r)
+        if (item[r]) l.item[l.hist[at[r] >> 16] + (at[r] & 0xFFFF)] = item[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kMaxChunk / kWide; ++r) {
+        const unsigned j = r * kWide + threadIdx.x;
+        if (j >= total) break;
+        const uint64_t w = l.item[j];
+        out[l.region[bin_of(w)] + j] = w;
+    }
 }
 
 // One chunk per workgroup: equal codes are merged in an LDS table (a Zipf
@@ -188,13 +259,12 @@ __global__ __launch_bounds__(kWide) void k_partition(const int32_t* __restrict__
                                                      unsigned* __restrict__ cursors,
                                                      uint64_t* __restrict__ items) {
     constexpr int R = kMaxChunk / kWide;
-    static_assert(kMaxBuckets == kWide, "a thread per bucket");
-    __shared__ unsigned long long s_item[kMaxChunk];
-    __shared__ unsigned s_hist[kMaxBuckets], s_region[kMaxBuckets], s_wave[kWide / 64];
+    __shared__ PartLds l;
+    auto& s_item = l.item;
     const int buckets = 1 << log2_buckets;
 #pragma unroll
     for (int r = 0; r < R; ++r) s_item[r * kWide + threadIdx.x] = 0;
-    for (int b = threadIdx.x; b < buckets; b += kWide) s_hist[b] = 0;
+    l.hist[threadIdx.x] = 0;
     __syncthreads();
     uint64_t key[R];
     bool bad_token = false;
@@ -228,59 +298,141 @@ __global__ __launch_bounds__(kWide) void k_partition(const int32_t* __restrict__
         }
     }
     __syncthreads();
-    // Every item's bucket and its rank among the chunk's items there.
-    uint64_t item[R];
-    unsigned at[R], at_own[R];
+    // What the table merged and what found no slot in it.
+    uint64_t item[2 * R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        item[r] = s_item[r * kWide + threadIdx.x];
-        if (item[r]) {
-            const uint32_t b = bucket_of(count_hash(item[r] >> kCountBits), log2_buckets);
-            at[r] = b << 16 | atomicAdd(&s_hist[b], 1u);
-        }
-        if (key[r] != kEmptyKey) {
-            const uint32_t b = bucket_of(count_hash(key[r]), log2_buckets);
-            at_own[r] = b << 16 | atomicAdd(&s_hist[b], 1u);
+        item[2 * r] = s_item[r * kWide + threadIdx.x];
+        item[2 * r + 1] = key[r] != kEmptyKey ? key[r] << kCountBits | 1 : 0;
+    }
+    write_by_bin(
+        item, buckets,
+        [=](uint64_t w) { return bucket_of(count_hash(w >> kCountBits), log2_buckets); },
+        cursors + blockIdx.x % kGroups, kGroups, items, l);
+}
+
+// --------------------------------------------------------- a second level --
+// A bucket of a large corpus has more codes than a table takes by a factor that
+// grows with the corpus, and reading it once per part would make the scan's
+// cost quadratic (1.07G positions of nearly distinct 2-grams: 587 ms a call).
+// Above kSplitFrom positions the hash's next log2_subs bits split every bucket
+// once more, for one reading to count, one to write and 8 bytes written per item
+// (84 ms).  A bucket's items are taken in slices of kMaxChunk, in turn by the
+// workgroups of its row of the grid.
+
+// A bucket's items, from its regions: item j of the bucket is items[j + shift]
+// of the region it lies in.
+template <int kRegions>
+struct BucketItems {
+    unsigned upto[kRegions], shift[kRegions], total;
+
+    __device__ __forceinline__ BucketItems(const unsigned* __restrict__ begin,
+                                           const unsigned* __restrict__ end) {
+        total = 0;
+#pragma unroll
+        for (int g = 0; g < kRegions; ++g) {
+            shift[g] = begin[g] - total;
+            total += end[g] - begin[g];
+            upto[g] = total;
         }
     }
+    __device__ __forceinline__ unsigned at(unsigned j) const {
+        unsigned sh = shift[0];
+#pragma unroll
+        for (int g = 1; g < kRegions; ++g) {
+            // values, not a choice of addresses, which would keep the arrays in memory
+            const unsigned u = upto[g - 1], v = shift[g];
+            sh = j >= u ? v : sh;
+        }
+        return j + sh;
+    }
+};
+
+// How many of each bucket's items go to each of its sub-buckets.
+__global__ __launch_bounds__(kWide) void k_sub_sizes(const uint64_t* __restrict__ items,
+                                                     const unsigned* __restrict__ starts,
+                                                     const unsigned* __restrict__ cursors,
+                                                     int log2_buckets, int log2_subs,
+                                                     unsigned* __restrict__ sub_sizes) {
+    constexpr int R = kMaxChunk / kWide;
+    __shared__ unsigned s_hist[kMaxBuckets];
+    const unsigned b = blockIdx.y;
+    const BucketItems<kGroups> in(starts + b * kGroups, cursors + b * kGroups);
+    if (blockIdx.x * kMaxChunk >= in.total) return;
+    s_hist[threadIdx.x] = 0;
     __syncthreads();
-    // A thread per bucket: where its items start, in LDS and in its region.
-    const int b = threadIdx.x, lane = b & 63;
-    const unsigned mine = b < buckets ? s_hist[b] : 0;
-    unsigned inc = mine;
+    for (unsigned j0 = blockIdx.x * kMaxChunk; j0 < in.total; j0 += gridDim.x * kMaxChunk) {
+        uint64_t w[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const unsigned j = j0 + r * kWide + threadIdx.x;
+            w[r] = j < in.total ? items[in.at(j)] : 0;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (w[r])
+                atomicAdd(&s_hist[part_of(count_hash(w[r] >> kCountBits), log2_buckets,
+                                          log2_subs)], 1u);
+    }
+    lds_settled_barrier();
+    if (threadIdx.x < 1u << log2_subs && s_hist[threadIdx.x])
+        atomicAdd(sub_sizes + ((size_t)b << log2_subs) + threadIdx.x, s_hist[threadIdx.x]);
+}
+
+// Where the sub-buckets of each bucket start: one after another from the
+// bucket's own start.  One workgroup per bucket, a thread per sub-bucket.
+__global__ __launch_bounds__(kWide) void k_sub_offsets(const unsigned* __restrict__ starts,
+                                                       const unsigned* __restrict__ sub_sizes,
+                                                       int log2_subs,
+                                                       unsigned* __restrict__ sub_starts,
+                                                       unsigned* __restrict__ sub_cursors) {
+    __shared__ unsigned s_wave[kWide / 64];
+    const unsigned s = threadIdx.x, b = blockIdx.x, lane = s & 63;
+    const bool on = s < 1u << log2_subs;
+    const size_t i = ((size_t)b << log2_subs) + s;
+    const unsigned v = on ? sub_sizes[i] : 0;
+    unsigned inc = v;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const unsigned y = (unsigned)__shfl_up((int)inc, o);
-        if (lane >= o) inc += y;
+        if (lane >= (unsigned)o) inc += y;
     }
-    if (lane == 63) s_wave[b >> 6] = inc;
-    const unsigned region =
-        mine ? atomicAdd(cursors + b * kGroups + blockIdx.x % kGroups, mine) : 0;
+    if (lane == 63) s_wave[s >> 6] = inc;
     __syncthreads();
-    unsigned start = inc - mine, total = 0;
-    for (int w = 0; w < kWide / 64; ++w) {
-        if (w < b >> 6) start += s_wave[w];
-        total += s_wave[w];
-    }
-    s_hist[b] = start;
-    s_region[b] = region - start;
-    __syncthreads();
-    // The items by bucket in LDS, so that neighbouring lanes write neighbouring
-    // items: one store transaction per run where one per item (8 bytes at 64
-    // places per wavefront) ran at the rate of random accesses.
+    unsigned at = starts[(size_t)b * kGroups] + inc - v;
+    for (unsigned w = 0; w < s >> 6; ++w) at += s_wave[w];
+    if (on) sub_starts[i] = sub_cursors[i] = at;
+    // the end mark
+    if (s == 0 && b == gridDim.x - 1) sub_starts[(size_t)gridDim.x << log2_subs] =
+        starts[(size_t)gridDim.x * kGroups];
+}
+
+__global__ __launch_bounds__(kWide) void k_split(const uint64_t* __restrict__ items,
+                                                 const unsigned* __restrict__ starts,
+                                                 const unsigned* __restrict__ cursors,
+                                                 int log2_buckets, int log2_subs,
+                                                 unsigned* __restrict__ sub_cursors,
+                                                 uint64_t* __restrict__ out) {
+    constexpr int R = kMaxChunk / kWide;
+    __shared__ PartLds l;
+    const unsigned b = blockIdx.y;
+    const BucketItems<kGroups> in(starts + b * kGroups, cursors + b * kGroups);
+    for (unsigned j0 = blockIdx.x * kMaxChunk; j0 < in.total; j0 += gridDim.x * kMaxChunk) {
+        uint64_t w[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (item[r]) s_item[s_hist[at[r] >> 16] + (at[r] & 0xFFFF)] = item[r];
-        if (key[r] != kEmptyKey)
-            s_item[s_hist[at_own[r] >> 16] + (at_own[r] & 0xFFFF)] = key[r] << kCountBits | 1;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const unsigned j = r * kWide + threadIdx.x;
-        if (j >= total) break;
-        const uint64_t w = s_item[j];
-        items[s_region[bucket_of(count_hash(w >> kCountBits), log2_buckets)] + j] = w;
+        for (int r = 0; r < R; ++r) {
+            const unsigned j = j0 + r * kWide + threadIdx.x;
+            w[r] = j < in.total ? items[in.at(j)] : 0;
+        }
+        __syncthreads();  // the last slice has been written out
+        l.hist[threadIdx.x] = 0;
+        __syncthreads();
+        write_by_bin(
+            w, 1 << log2_subs,
+            [=](uint64_t x) {
+                return (uint32_t)part_of(count_hash(x >> kCountBits), log2_buckets, log2_subs);
+            },
+            sub_cursors + ((size_t)b << log2_subs), 1, out, l);
     }
 }
 
@@ -294,6 +446,7 @@ __global__ __launch_bounds__(kWide) void k_partition(const int32_t* __restrict__
 constexpr int kBucketSlots = 8192;
 constexpr int kBucketProbe = 64;
 
+template <int kRegions>  // regions per bucket: kGroups, or 1 on the second level
 __global__ __launch_bounds__(kWide) void k_bucket(
     const uint64_t* __restrict__ items, const unsigned* __restrict__ starts,
     const unsigned* __restrict__ cursors, int log2_buckets, uint32_t min_count, int level,
@@ -305,16 +458,9 @@ __global__ __launch_bounds__(kWide) void k_bucket(
     __shared__ unsigned long long s_key[kBucketSlots];
     __shared__ unsigned s_cnt[kBucketSlots];
     __shared__ unsigned s_full, s_ns, s_nc, s_mx;
-    const unsigned* begin = starts + blockIdx.x * kGroups;
-    const unsigned* end = cursors + blockIdx.x * kGroups;
-    // item j of the bucket is items[j + shift of its region]
-    unsigned upto[kGroups], shift[kGroups], total = 0;
-#pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
-        shift[g] = begin[g] - total;
-        total += end[g] - begin[g];
-        upto[g] = total;
-    }
+    const BucketItems<kRegions> in(starts + (size_t)blockIdx.x * kRegions,
+                                   cursors + (size_t)blockIdx.x * kRegions);
+    const unsigned total = in.total;
     if (total == 0) return;
     // A table of at least twice the items, where they are few, up to kBucketSlots.
     unsigned slots = kWide;
@@ -337,10 +483,7 @@ __global__ __launch_bounds__(kWide) void k_bucket(
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const unsigned j = j0 + r * kWide + threadIdx.x;
-                unsigned sh = shift[0];
-#pragma unroll
-                for (int g = 1; g < kGroups; ++g) sh = j >= upto[g - 1] ? shift[g] : sh;
-                w[r] = j < total ? items[j + sh] : 0;
+                w[r] = j < total ? items[in.at(j)] : 0;
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -450,15 +593,6 @@ __global__ __launch_bounds__(kThreads) void k_surv_insert(const unsigned* __rest
             s = (s + 1) & mask;
         t[s].dense = (int32_t)id;
     }
-}
-
-// __syncthreads after this wavefront's LDS operations have completed.  The
-// barrier alone is meant to do that, but in k_ids the compiler (ROCm 7.2)
-// leaves the wait out on the paths from the counting adds to it, and a
-// wavefront's counts were then missing from the sums now and then.
-__device__ __forceinline__ void lds_settled_barrier() {
-    __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
-    __syncthreads();
 }
 
 // Dense id of the survivor of scan n ending at every position, or -1, and the
@@ -725,7 +859,8 @@ namespace {
 // at different times shares memory: a scan's items (8 bytes per position) lie
 // where its survivors' table (at least 32) is made once they are counted, the
 // region starts and cursors where the ids of the scan's end are written
-// (k_ids, after their last use), the bucket sizes in the histogram's place.
+// (k_ids, after their last use; the second level's items behind the first's, its
+// starts and cursors behind theirs), the bucket sizes in the histogram's place.
 struct DiscLayout {
     uint64_t cap;
     int64_t cand_cap;
@@ -765,14 +900,25 @@ DiscLayout disc_layout(int64_t BT, int max_len) {
 struct Shape {
     uint32_t chunk, n_chunks;
     int log2_buckets;
+    int log2_subs;  // sub-buckets of each bucket, 0 for no second level
 };
 
+// Above this many positions buckets are split once more, into sub-buckets of up to
+// 8,192 positions each, at most 256 per bucket.  Whole calls without / with the
+// second level: Zipf(1.1) tokens, K = 3, 20M positions 1.29 / 1.55 ms, 25M 1.95 /
+// 2.20, 33.5M 2.82 / 2.33, 268M 33.3 / 16.8, K = 5, 33.5M 4.3 / 4.5; uniform tokens
+// (2-grams nearly distinct), K = 3, 20M 2.20 / 1.32, 268M 59.7 / 24.0, K = 2, 537M
+// 175 / 41 ms.  A stream of text is the first kind, and the line lies where it gains.
+constexpr int64_t kSplitFrom = 1ll << 25;
+
 Shape scan_shape(int64_t BT) {
-    Shape s{kWide, 0, 0};
+    Shape s{kWide, 0, 0, 0};
     while (s.chunk < kMaxChunk && BT / (2 * (int64_t)s.chunk) >= 256) s.chunk *= 2;
     s.n_chunks = (uint32_t)((BT + s.chunk - 1) / s.chunk);
     while ((4096ll << s.log2_buckets) < BT && (1 << s.log2_buckets) < kMaxBuckets)
         ++s.log2_buckets;
+    if (BT > kSplitFrom)
+        while ((8192ll << (s.log2_buckets + s.log2_subs)) < BT) ++s.log2_subs;
     return s;
 }
 
@@ -883,14 +1029,39 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
     int32_t* ids_cur = ids_b;
     for (int n = 2; n <= max_len && rc == SCONE_OK; ++n) {
         unsigned* starts = reinterpret_cast<unsigned*>(ids_cur);
-        unsigned* cursors = starts + ((size_t)kGroups << sh.log2_buckets);
+        unsigned* cursors = starts + ((size_t)kGroups << sh.log2_buckets) + 1;
+        const uint64_t* counted = items;  // what k_bucket counts, and its regions
+        const unsigned *c_starts = starts, *c_cursors = cursors;
+        const int log2_counted = sh.log2_buckets + sh.log2_subs;
         hipLaunchKernelGGL(k_offsets, dim3(1), dim3(kMaxBuckets), 0, st, sizes,
                            1 << sh.log2_buckets, starts, cursors, ctr + 1);
         hipLaunchKernelGGL(n == 2 ? k_partition<true> : k_partition<false>, dim3(sh.n_chunks),
                            wide, 0, st, token_ids, n_tok, row, ids_prev, sh.chunk,
                            sh.log2_buckets, cursors, items);
-        hipLaunchKernelGGL(k_bucket, dim3(1u << sh.log2_buckets), wide, 0, st, items, starts,
-                           cursors, sh.log2_buckets, (uint32_t)min_count, n, n == 2 ? 1 : 0,
+        if (sh.log2_subs) {
+            const size_t subs = (size_t)1 << log2_counted;
+            unsigned* sub_starts = cursors + ((size_t)kGroups << sh.log2_buckets);
+            unsigned* sub_cursors = sub_starts + subs + 1;
+            unsigned* sub_sizes = sub_cursors + subs;
+            uint64_t* sub_items = items + BT;
+            // as many workgroups per bucket as its share of the positions has slices
+            const dim3 grid((unsigned)(((BT >> sh.log2_buckets) + kMaxChunk) / kMaxChunk),
+                            1u << sh.log2_buckets);
+            if (hipMemsetAsync(sub_sizes, 0, subs * sizeof(unsigned), st) != hipSuccess)
+                rc = SCONE_EHIP;
+            hipLaunchKernelGGL(k_sub_sizes, grid, wide, 0, st, items, starts, cursors,
+                               sh.log2_buckets, sh.log2_subs, sub_sizes);
+            hipLaunchKernelGGL(k_sub_offsets, dim3(1u << sh.log2_buckets), wide, 0, st, starts,
+                               sub_sizes, sh.log2_subs, sub_starts, sub_cursors);
+            hipLaunchKernelGGL(k_split, grid, wide, 0, st, items, starts, cursors,
+                               sh.log2_buckets, sh.log2_subs, sub_cursors, sub_items);
+            counted = sub_items;
+            c_starts = sub_starts;
+            c_cursors = sub_cursors;
+        }
+        hipLaunchKernelGGL(sh.log2_subs ? k_bucket<1> : k_bucket<kGroups>,
+                           dim3(1u << log2_counted), wide, 0, st, counted, c_starts,
+                           c_cursors, log2_counted, (uint32_t)min_count, n, n == 2 ? 1 : 0,
                            ctr + 1, n < max_len ? skeys[n] : nullptr, ctr + 2, cand_key,
                            cand_count, cand_level, ctr + 3);
         if (n < max_len) {

@@ -3,6 +3,7 @@
 bucket and many, chunks of every length, remainders, buckets with more codes
 than one LDS table holds, one n-gram at every position."""
 import ctypes
+import time
 
 import numpy as np
 import pytest
@@ -49,6 +50,7 @@ def ordered(rows):
 def check_all(X, K, min_count):
     """Every candidate, tokens and count, when S takes them all."""
     want = scans(X, K, min_count)
+    assert int(want[:, :K].max()) < 65_536  # torch's own rows: wrong past 2 GiB of them
     fg, ln, ct = S.discover_fgrams(X, K, want.shape[0] + 5, min_count)
     got = torch.cat([fg, ct[:, None]], 1).long()
     assert got.shape == want.shape
@@ -110,3 +112,34 @@ def test_rejected_corpus_leaves_the_outputs(where):
     assert rc == S.scone.ETOKEN and n.value == 0
     for t in (fg, ln, ct):
         assert (t == -77).all()
+
+
+# Both sides of the line where buckets are split once more, and the next number
+# of sub-buckets; many and few codes per bucket, codes that fill one bucket.
+@pytest.mark.parametrize("B,T", [(8192, 4096), (8193, 4096), (16_385, 4099)])
+@pytest.mark.parametrize("V", [1, 50, 65_536])
+def test_second_level(B, T, V):
+    g = torch.Generator(device="cuda").manual_seed(B)
+    X = torch.randint(0, V, (B, T), device="cuda", generator=g, dtype=torch.int32)
+    K = 2 if V == 65_536 and B * T > 1 << 26 else 3   # rows of the reference below 2 GiB
+    check_all(X, K, 1 if V == 65_536 else 2)
+
+
+def test_cost_is_linear_in_the_corpus():
+    """Nearly distinct 2-grams: 32 times the positions take about 32 times as
+    long (reading buckets once per part took 170 times as long)."""
+    def per_position(B):
+        X = torch.randint(0, 65_536, (B, 4096), device="cuda", dtype=torch.int32,
+                          generator=torch.Generator(device="cuda").manual_seed(1))
+        best = float("inf")
+        for _ in range(3):
+            torch.cuda.synchronize()
+            start = time.perf_counter()
+            S.discover_fgrams(X, 2, 1000, 1)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - start)
+        del X
+        torch.cuda.empty_cache()
+        return best / (B * 4096)
+
+    assert per_position(131_072) < 2.5 * per_position(4096)
