@@ -274,13 +274,13 @@ int build_sizes_ok(int64_t n, int32_t max_len, double max_load) {
 }
 
 // Slots for these lengths: the smallest power of two >= max(64, entries /
-// max_load).  Lengths of 4 and more are counted on the device, in `ctl` (zeroed
-// here); waits for the stream where there can be any.
+// max_load).  Where there can be lengths of 4 and more they are counted on the
+// device, in `ctl`, and the call waits for the stream; else it does nothing there.
 int count_slots(const int32_t* lengths, int64_t n, int32_t max_len, double max_load,
                 Control* ctl, hipStream_t st, uint64_t& cap) {
     unsigned long long more[2] = {0, 0};
-    SCONE_HIP_TRY(hipMemsetAsync(ctl, 0, sizeof(Control), st));
     if (n > 0 && max_len >= 4) {
+        SCONE_HIP_TRY(hipMemsetAsync(ctl, 0, sizeof(Control), st));
         const int64_t blocks = (n + kBuildThreads - 1) / kBuildThreads;
         hipLaunchKernelGGL(k_count_long, dim3((unsigned)std::min<int64_t>(blocks, kCountBlocks)),
                            dim3(kBuildThreads), 0, st, lengths, n, (int)max_len, &ctl->long4);
@@ -301,6 +301,7 @@ int fill_table(const int32_t* fgrams, const int32_t* lengths, const int32_t* ids
                int32_t max_len, void* slots, uint64_t cap, Control* ctl, int dev, hipStream_t st,
                scone_table_t** out) {
     const int slot_bytes = slot_bytes_for(max_len);
+    SCONE_HIP_TRY(hipMemsetAsync(ctl, 0, sizeof(Control), st));
     SCONE_HIP_TRY(hipMemsetAsync(slots, 0, cap * (uint64_t)slot_bytes, st));
     if (n > 0) {
         const hipError_t e =
@@ -382,7 +383,10 @@ extern "C" int scone_fgram_table_bytes(const int32_t* lengths, int64_t n, int32_
     uint64_t cap = 0;
     rc = count_slots(lengths, n, max_len, max_load, static_cast<Control*>(scratch),
                      static_cast<hipStream_t>(stream), cap);
-    if (rc == SCONE_OK) *bytes = (int64_t)(cap * (uint64_t)slot_bytes_for(max_len)) + kControlBytes;
+    if (rc == SCONE_OK)
+        *bytes = (int64_t)(cap * (uint64_t)slot_bytes_for(max_len)) + kControlBytes;
+    else  // the scratch is the caller's again, whatever was queued there
+        (void)hipStreamSynchronize(static_cast<hipStream_t>(stream));
     return rc;
 }
 
@@ -408,11 +412,13 @@ extern "C" int scone_build_fgram_table_in(const int32_t* fgrams, const int32_t* 
     Control* ctl = static_cast<Control*>(memory);
     uint64_t cap = 0;
     rc = count_slots(lengths, n, max_len, max_load, ctl, st, cap);
-    if (rc != SCONE_OK) return rc;
-    if ((uint64_t)memory_bytes < cap * (uint64_t)slot_bytes_for(max_len) + kControlBytes)
-        return SCONE_EINVAL;
-    rc = fill_table(fgrams, lengths, ids, n, max_len,
-                    static_cast<uint8_t*>(memory) + kControlBytes, cap, ctl, dev, st, out);
+    if (rc == SCONE_OK &&
+        (uint64_t)memory_bytes < cap * (uint64_t)slot_bytes_for(max_len) + kControlBytes)
+        rc = SCONE_EINVAL;
+    if (rc == SCONE_OK)
+        rc = fill_table(fgrams, lengths, ids, n, max_len,
+                        static_cast<uint8_t*>(memory) + kControlBytes, cap, ctl, dev, st, out);
+    // the memory is the caller's again, whatever was queued there
     if (rc != SCONE_OK) (void)hipStreamSynchronize(st);
     return rc;
 }

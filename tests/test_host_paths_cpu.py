@@ -1,0 +1,96 @@
+"""The library's host paths against a stand-in for the HIP runtime (CPU only).
+
+A small C library with the runtime calls that a path makes is preloaded in a
+process of its own: it launches nothing, notes every call in order, hands out
+the words that a read-back from the device would give and can let a wait fail.
+"""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2502_01637_amd", "libscone.so")
+
+STUB = r"""
+#include <stddef.h>
+#include <string.h>
+typedef struct { unsigned x, y, z; } dim3;
+char stub_log[65536];
+static size_t used;
+unsigned stub_words[16];      /* what a read-back gives, then zeros */
+int stub_fail_sync, stub_syncs;
+static void note(char c) { if (used + 1 < sizeof(stub_log)) stub_log[used++] = c; }
+int hipMemsetAsync(void* p, int v, size_t n, void* s) { note('M'); return 0; }
+int hipMemcpyAsync(void* d, const void* s, size_t n, int kind, void* st) {
+    note(kind == 2 ? 'D' : 'U');
+    if (kind == 2) {
+        memset(d, 0, n);
+        memcpy(d, stub_words, n < sizeof(stub_words) ? n : sizeof(stub_words));
+    }
+    return 0;
+}
+int hipStreamSynchronize(void* s) { note('S'); return ++stub_syncs == stub_fail_sync; }
+int hipLaunchKernel(const void* f, dim3 g, dim3 b, void** a, size_t n, void* s) {
+    note('K');
+    return 0;
+}
+int __hipPushCallConfiguration(dim3 g, dim3 b, size_t n, void* s) { return 0; }
+int __hipPopCallConfiguration(dim3* g, dim3* b, size_t* n, void** s) {
+    dim3 one = {1, 1, 1};
+    *g = *b = one;
+    *n = 0;
+    *s = 0;
+    return 0;
+}
+int hipGetLastError(void) { return 0; }
+int hipGetDevice(int* d) { *d = 0; return 0; }
+"""
+
+HEAD = textwrap.dedent("""
+    import ctypes, struct, sys
+    P, I64, I32, D = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_double
+    stub = ctypes.CDLL(sys.argv[1])
+    L = ctypes.CDLL(sys.argv[2])
+    log = lambda: ctypes.c_char_p(ctypes.addressof(ctypes.c_char.in_dll(stub, "stub_log"))).value
+    words = (ctypes.c_uint * 16).in_dll(stub, "stub_words")
+    fail_sync = ctypes.c_int.in_dll(stub, "stub_fail_sync")
+    A = 0x7f0000000000          # addresses that nothing touches
+""")
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    d = tmp_path_factory.mktemp("stub")
+    src, so = d / "stub.c", d / "stub.so"
+    src.write_text(STUB)
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
+    return str(so)
+
+
+def run(stub, body):
+    env = dict(os.environ)
+    env["LD_PRELOAD"] = ":".join(p for p in (stub, os.environ.get("LD_PRELOAD", "")) if p)
+    p = subprocess.run([sys.executable, "-c", HEAD + textwrap.dedent(body), stub, LIB], env=env,
+                       capture_output=True, text=True, timeout=120)
+    assert p.returncode == 0, p.stderr[-2000:]
+    return p.stdout.split()
+
+
+@pytest.mark.parametrize("max_len", [2, 3, 4, 7])
+@pytest.mark.parametrize("n", [0, 1000])
+def test_table_sizes_leave_nothing_queued(stub, max_len, n):
+    """scone_fgram_table_bytes, and a build that is refused for a short
+    memory, have nothing queued in the caller's memory when they return."""
+    for call in ("L.scone_fgram_table_bytes(P(A), I64(n), I32(K), D(0.5), P(A + (1 << 20)), None,"
+                 " ctypes.byref(b))",
+                 "L.scone_build_fgram_table_in(P(A), P(A + (1 << 20)), P(A + (2 << 20)), I64(n),"
+                 " I32(K), D(0.5), P(A + (3 << 20)), I64(300), None, ctypes.byref(h))"):
+        out = run(stub, f"""
+            n, K, b, h = {n}, {max_len}, I64(), P()
+            print({call}, "log=" + log().decode())
+        """)
+        assert out[0] == ("0" if "bytes(" in call else "1")
+        assert out[1] == "log=" or out[1].endswith("S"), out
