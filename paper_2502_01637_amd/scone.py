@@ -122,7 +122,9 @@ def _check(rc: int, what: str):
 # Stream object (2.7 us) and torch.cuda.device() switches devices twice (1.4 us)
 # where the handle and an equal device index take 0.1 and 0.3 us: a decoding step
 # took 13.1 us, now 8.2, a 16 x 512 prefill 13.6, now 9.0.
-_raw_stream = torch._C._cuda_getCurrentRawStream
+# (A torch built without GPU support has no such function; nothing that needs a
+# stream runs there, but the package imports.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _HERE = contextlib.nullcontext()
 
 
