@@ -202,13 +202,13 @@ class Table:
 
     def close(self):
         if self._h is not None:
-            lib().scone_table_destroy(self._h)
-            self._h = None
             if self._memory is not None:
                 # lookups on any stream may still read the slots: wait, as
                 # freeing device memory does, before the allocator has them back
-                memory, self._memory = self._memory, None
-                torch.cuda.synchronize(memory.device)
+                # (where waiting is refused, under capture, the table stays)
+                torch.cuda.synchronize(self._memory.device)
+            lib().scone_table_destroy(self._h)
+            self._h = self._memory = None
 
     def __del__(self):
         try:

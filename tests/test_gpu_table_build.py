@@ -117,3 +117,24 @@ def test_size_arguments():
     assert L.scone_fgram_table_bytes(None, 0, 3, 0.5, None, None, None) == S.scone.EINVAL
     assert L.scone_fgram_table_bytes(None, 0, 3, 0.5, None, None,
                                      ctypes.byref(b)) == S.scone.EINVAL
+
+
+@pytest.mark.gpu
+def test_close_that_cannot_wait_keeps_the_table(monkeypatch):
+    """Where the wait for running lookups is refused (under capture), the error
+    is raised and the table stays whole until it can be closed."""
+    fg = np.array([[1, 2], [3, 4]], dtype=np.int32)
+    t = build_gpu(fg, np.full(2, 2, np.int32), np.array([10, 11], np.int32))
+
+    def refused(device=None):
+        raise RuntimeError("operation not permitted when stream is capturing")
+
+    with monkeypatch.context() as m:
+        m.setattr(torch.cuda, "synchronize", refused)
+        with pytest.raises(RuntimeError):
+            t.close()
+    X = dev(np.array([[1, 2, 3, 4]], dtype=np.int32))
+    ids, _ = S.lookup(t, X, 2)
+    S.check_ok()
+    assert ids.tolist() == [[1, 10, 3, 11]]
+    t.close()
