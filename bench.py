@@ -1070,10 +1070,14 @@ def fgram_model_flops(fgrams: np.ndarray, lengths: np.ndarray, d: int, d_ff: int
     if n_layers == 0:
         return 0.0
     att = 0.0 if products_only else 1.0
-    # states at depth i: the f-grams that end there and the distinct prefixes of longer ones
-    states = [int((lengths == i + 1).sum())
-              + len(np.unique(fgrams[lengths > i + 1, :i + 1], axis=0))
-              for i in range(int(lengths.max()))]
+    # states at depth i: the f-grams that end there and the distinct prefixes of longer
+    # ones that are not such an f-gram (its state serves them too)
+    states = []
+    for i in range(int(lengths.max())):
+        own = fgrams[lengths == i + 1, :i + 1]
+        mine = len(np.unique(own, axis=0)) if len(own) else 0
+        both = np.concatenate([own, fgrams[lengths > i + 1, :i + 1]])
+        states.append(len(own) + len(np.unique(both, axis=0)) - mine)
     row = 2.0 * (4.0 * d * d + 2.0 * d * d_ff)
     full = sum(m * (row + att * 4.0 * d * (i + 1)) for i, m in enumerate(states))
     last = (sum(states) * 2.0 * 3.0 * d * d + len(lengths) * 2.0 * (d * d + 2.0 * d * d_ff)

@@ -163,3 +163,23 @@ def test_kernel_sources_names_the_defining_files_and_their_headers():
             "runtime.hip"} <= set(srcs)
     assert "gemm_bf16.h" not in srcs and "discover.hip" not in srcs
     assert "gemm_bf16.h" in bench.kernel_sources({"k_gemm<1, 256, 256, 4, 2, false>"})
+
+
+def test_fgram_model_flops_counts_each_state_once():
+    """(a, b) and its copy have states of their own at depth 1; (a, b, c) and
+    (a, b, d) take theirs from there, (a, e, f) brings its own."""
+    fg = np.array([[1, 2, -1], [1, 2, -1], [1, 2, 3], [1, 2, 4], [1, 5, 6]], dtype=np.int32)
+    ln = np.array([2, 2, 3, 3, 3])
+    d, ff = 512, 1024
+    states = [1, 3, 3]                       # by depth: a; 2 x (a, b), (a, e); three ends
+    row = 2 * (4 * d * d + 2 * d * ff)
+    last = 7 * 2 * 3 * d * d + 5 * 2 * (d * d + 2 * d * ff)
+    got = bench.fgram_model_flops(fg, ln, d, ff, 3, products_only=True)
+    assert got == 2 * 7 * row + last
+    att = 4 * d * sum(m * (i + 1) for i, m in enumerate(states))
+    got = bench.fgram_model_flops(fg, ln, d, ff, 3)
+    assert got == 2 * (7 * row + att) + last + 4 * d * ln.sum()
+    # lengths 2 and 3 that share nothing: one state per token
+    got = bench.fgram_model_flops(np.array([[1, 2, -1], [3, 4, 5]]), np.array([2, 3]), d, ff, 2,
+                                  products_only=True)
+    assert got == 5 * row + 5 * 2 * 3 * d * d + 2 * 2 * (d * d + 2 * d * ff)
