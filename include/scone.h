@@ -48,7 +48,8 @@ enum scone_status {
     SCONE_ELEN = 2,    /* an f-gram length outside [2, max_len] */
     SCONE_EID = 3,     /* an f-gram id outside [0, 2^31 - 1) */
     SCONE_EDUP = 4,    /* the same f-gram appears twice in the build input */
-    SCONE_EFULL = 5,   /* hash table has no free slot (cannot happen for max_load <= 0.9) */
+    SCONE_EFULL = 5,   /* hash table has no free slot (cannot happen for max_load <= 0.9), or
+                        * discovery's own counts disagree (a check that should never fail) */
     SCONE_ENOMEM = 6,  /* device or pinned host allocation failed */
     SCONE_EHIP = 7,    /* a HIP runtime call failed */
     SCONE_ETOKEN = 8,  /* a token outside [0, SCONE_TOKEN_LIMIT) */

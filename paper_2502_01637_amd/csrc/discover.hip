@@ -321,16 +321,22 @@ __global__ __launch_bounds__(kWide) void k_partition(const int32_t* __restrict__
 // workgroups of its row of the grid.
 
 // A bucket's items, from its regions: item j of the bucket is items[j + shift]
-// of the region it lies in.
+// of the region it lies in.  `whole` says that no region has passed the start of
+// the next: the pass that counted the regions and the one that filled them agree.
+// They are different kernels, and a count that is lost (see lds_settled_barrier)
+// would otherwise put one bucket's items over another's with no error.
 template <int kRegions>
 struct BucketItems {
     unsigned upto[kRegions], shift[kRegions], total;
+    bool whole;
 
     __device__ __forceinline__ BucketItems(const unsigned* __restrict__ begin,
                                            const unsigned* __restrict__ end) {
         total = 0;
+        whole = true;
 #pragma unroll
         for (int g = 0; g < kRegions; ++g) {
+            whole &= end[g] <= begin[g + 1];
             shift[g] = begin[g] - total;
             total += end[g] - begin[g];
             upto[g] = total;
@@ -353,11 +359,16 @@ __global__ __launch_bounds__(kWide) void k_sub_sizes(const uint64_t* __restrict_
                                                      const unsigned* __restrict__ starts,
                                                      const unsigned* __restrict__ cursors,
                                                      int log2_buckets, int log2_subs,
-                                                     unsigned* __restrict__ sub_sizes) {
+                                                     unsigned* __restrict__ sub_sizes,
+                                                     unsigned* __restrict__ status) {
     constexpr int R = kMaxChunk / kWide;
     __shared__ unsigned s_hist[kMaxBuckets];
     const unsigned b = blockIdx.y;
     const BucketItems<kGroups> in(starts + b * kGroups, cursors + b * kGroups);
+    if (!in.whole) {
+        if (threadIdx.x == 0) atomicOr(status, err_bit(SCONE_EFULL));
+        return;
+    }
     if (blockIdx.x * kMaxChunk >= in.total) return;
     s_hist[threadIdx.x] = 0;
     __syncthreads();
@@ -417,6 +428,7 @@ __global__ __launch_bounds__(kWide) void k_split(const uint64_t* __restrict__ it
     __shared__ PartLds l;
     const unsigned b = blockIdx.y;
     const BucketItems<kGroups> in(starts + b * kGroups, cursors + b * kGroups);
+    if (!in.whole) return;
     for (unsigned j0 = blockIdx.x * kMaxChunk; j0 < in.total; j0 += gridDim.x * kMaxChunk) {
         uint64_t w[R];
 #pragma unroll
@@ -453,7 +465,7 @@ __global__ __launch_bounds__(kWide) void k_bucket(
     int keep_all, unsigned* __restrict__ n_surv, uint64_t* __restrict__ skey,
     unsigned* __restrict__ n_cand, uint64_t* __restrict__ cand_key,
     uint32_t* __restrict__ cand_count, int8_t* __restrict__ cand_level,
-    unsigned* __restrict__ max_count) {
+    unsigned* __restrict__ max_count, unsigned* __restrict__ status) {
     constexpr int R = kBucketSlots / kWide;
     __shared__ unsigned long long s_key[kBucketSlots];
     __shared__ unsigned s_cnt[kBucketSlots];
@@ -461,6 +473,10 @@ __global__ __launch_bounds__(kWide) void k_bucket(
     const BucketItems<kRegions> in(starts + (size_t)blockIdx.x * kRegions,
                                    cursors + (size_t)blockIdx.x * kRegions);
     const unsigned total = in.total;
+    if (!in.whole) {
+        if (threadIdx.x == 0) atomicOr(status, err_bit(SCONE_EFULL));
+        return;
+    }
     if (total == 0) return;
     // A table of at least twice the items, where they are few, up to kBucketSlots.
     unsigned slots = kWide;
@@ -1050,7 +1066,7 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
             if (hipMemsetAsync(sub_sizes, 0, subs * sizeof(unsigned), st) != hipSuccess)
                 rc = SCONE_EHIP;
             hipLaunchKernelGGL(k_sub_sizes, grid, wide, 0, st, items, starts, cursors,
-                               sh.log2_buckets, sh.log2_subs, sub_sizes);
+                               sh.log2_buckets, sh.log2_subs, sub_sizes, ctr + 0);
             hipLaunchKernelGGL(k_sub_offsets, dim3(1u << sh.log2_buckets), wide, 0, st, starts,
                                sub_sizes, sh.log2_subs, sub_starts, sub_cursors);
             hipLaunchKernelGGL(k_split, grid, wide, 0, st, items, starts, cursors,
@@ -1063,7 +1079,7 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
                            dim3(1u << log2_counted), wide, 0, st, counted, c_starts,
                            c_cursors, log2_counted, (uint32_t)min_count, n, n == 2 ? 1 : 0,
                            ctr + 1, n < max_len ? skeys[n] : nullptr, ctr + 2, cand_key,
-                           cand_count, cand_level, ctr + 3);
+                           cand_count, cand_level, ctr + 3, ctr + 0);
         if (n < max_len) {
             hipLaunchKernelGGL(k_surv_clear, dim3(g_surv), narrow, 0, st, ctr + 1, table);
             hipLaunchKernelGGL(k_surv_insert, dim3(g_surv), narrow, 0, st, ctr + 1, skeys[n],
@@ -1102,7 +1118,7 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
         hipLaunchKernelGGL(k_cut, dim3(1), wide, 0, st, hist, ctr + 2, S, cut);
         if (!select() || !read_counters()) rc = SCONE_EHIP;
     }
-    if (rc == SCONE_OK && h[0]) rc = SCONE_ETOKEN;
+    if (rc == SCONE_OK && h[0]) rc = (h[0] & err_bit(SCONE_ETOKEN)) ? SCONE_ETOKEN : SCONE_EFULL;
     const int64_t n_cand = h[2];
     const uint32_t max_c = h[3];
     Cut found{};

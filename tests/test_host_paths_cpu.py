@@ -94,3 +94,18 @@ def test_table_sizes_leave_nothing_queued(stub, max_len, n):
         """)
         assert out[0] == ("0" if "bytes(" in call else "1")
         assert out[1] == "log=" or out[1].endswith("S"), out
+
+
+def test_discovery_tells_its_two_data_errors_apart(stub):
+    """The status word's bits: a bad token, regions that disagree, and both."""
+    for bits, want in [(1 << 8, "8"), (1 << 5, "5"), (1 << 8 | 1 << 5, "8")]:
+        out = run(stub, f"""
+            words[0], words[2], words[3] = {bits}, 5, 3
+            found = I64(-1)
+            a = lambda k: P(A + (k << 24))
+            rc = L.scone_discover_fgrams(a(0), I64(10), I64(100), I32(3), I32(1), I64(20), a(1),
+                                         a(2), a(3), ctypes.byref(found), a(4), I64(1 << 24),
+                                         None)
+            print(rc, found.value)
+        """)
+        assert out == [want, "0"], (bits, out)
