@@ -1000,9 +1000,10 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
         }
         workspace = own;
     }
-    auto release = [&]() {
-        (void)hipStreamSynchronize(st);
+    auto release = [&]() {  // false if the stream's work failed
+        const bool done = hipStreamSynchronize(st) == hipSuccess;
         if (own) (void)hipFree(own);
+        return done;
     };
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     SurvSlot* table = reinterpret_cast<SurvSlot*>(ws + lay.table);
@@ -1154,7 +1155,7 @@ extern "C" int scone_discover_fgrams(const int32_t* token_ids, int64_t B, int64_
              !select()))
             rc = SCONE_EHIP;
     }
-    release();
+    if (!release() && rc == SCONE_OK) rc = SCONE_EHIP;
     if (rc == SCONE_OK) *n_found = n_cand < S ? n_cand : S;
     return rc;
 }

@@ -109,3 +109,22 @@ def test_discovery_tells_its_two_data_errors_apart(stub):
             print(rc, found.value)
         """)
         assert out == [want, "0"], (bits, out)
+
+
+def test_discovery_reports_a_failed_last_wait(stub):
+    """The second selection (a cut above the histogram) is waited for at the
+    end of the call; an error that this wait returns is the call's."""
+    for fail, want in [(0, "0"), (2, "7")]:
+        out = run(stub, f"""
+            words[2], words[3] = 50, 4095               # candidates, the largest count
+            words[8], words[9] = 4095, 1                # the cut is still to be found
+            fail_sync.value = {fail}
+            found = I64(-1)
+            a = lambda k: P(A + (k << 24))
+            rc = L.scone_discover_fgrams(a(0), I64(10), I64(100), I32(2), I32(1), I64(20), a(1),
+                                         a(2), a(3), ctypes.byref(found), a(4), I64(1 << 24),
+                                         None)
+            print(rc, found.value, log().decode())
+        """)
+        assert out[0] == want and out[1] == ("20" if want == "0" else "0"), out
+        assert out[2].endswith("DSUKS"), out
