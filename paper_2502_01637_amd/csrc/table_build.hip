@@ -273,13 +273,16 @@ int build_sizes_ok(int64_t n, int32_t max_len, double max_load) {
     return SCONE_OK;
 }
 
+// Whether there can be lengths of 4 and more, which take suffix entries.
+bool has_long(int64_t n, int32_t max_len) { return n > 0 && max_len >= 4; }
+
 // Slots for these lengths: the smallest power of two >= max(64, entries /
-// max_load).  Where there can be lengths of 4 and more they are counted on the
-// device, in `ctl`, and the call waits for the stream; else it does nothing there.
+// max_load).  Where has_long, the lengths are counted on the device, in `ctl`
+// (zeroed here), and the call waits for the stream; else it does nothing there.
 int count_slots(const int32_t* lengths, int64_t n, int32_t max_len, double max_load,
                 Control* ctl, hipStream_t st, uint64_t& cap) {
     unsigned long long more[2] = {0, 0};
-    if (n > 0 && max_len >= 4) {
+    if (has_long(n, max_len)) {
         SCONE_HIP_TRY(hipMemsetAsync(ctl, 0, sizeof(Control), st));
         const int64_t blocks = (n + kBuildThreads - 1) / kBuildThreads;
         hipLaunchKernelGGL(k_count_long, dim3((unsigned)std::min<int64_t>(blocks, kCountBlocks)),
@@ -301,7 +304,8 @@ int fill_table(const int32_t* fgrams, const int32_t* lengths, const int32_t* ids
                int32_t max_len, void* slots, uint64_t cap, Control* ctl, int dev, hipStream_t st,
                scone_table_t** out) {
     const int slot_bytes = slot_bytes_for(max_len);
-    SCONE_HIP_TRY(hipMemsetAsync(ctl, 0, sizeof(Control), st));
+    if (!has_long(n, max_len))  // else count_slots has zeroed them
+        SCONE_HIP_TRY(hipMemsetAsync(ctl, 0, sizeof(Control), st));
     SCONE_HIP_TRY(hipMemsetAsync(slots, 0, cap * (uint64_t)slot_bytes, st));
     if (n > 0) {
         const hipError_t e =
