@@ -632,11 +632,17 @@ inline hipError_t launch_tiles(const uint16_t* A, const uint16_t* W, const uint1
 //
 // The residual product takes the tile with the least rounds times the length of
 // one, in hundredths of a round of 256 x 256 tiles with a long sum: 116 with K up to
-// 1,024, 78 for 256 x 192, 70 for 128 x 128, two per compute unit, and 45 for their
-// last round where one per unit is enough.  Over 96 shapes (N 512 to 2,048, K = N and
-// 4 N, 700 to 30,000 rows) the choice is within 0.3% of the best on average and 10%
-// at most (6,800, 3,001 and 20,000 rows, N = 1,536, 1,536 and 1,024, K = 4 N: 256 x
-// 256 142, 122 and 200 us, 256 x 192 109, 110 us, 128 x 128 156, 87 and 179 us).
+// 384, 80 for 256 x 192 (90 with K up to 384), 68 for 128 x 128, two per compute unit,
+// and 45 for their last round where one per unit is enough.  Its 256 x 256 tiles are
+// k_gemm's where the sum is short (K up to 640) or the rounds are few (three, with K
+// up to 4,096): k_gemm_resid starts and ends 1 to 2 us later, and gains that back
+// with its residual loads over longer sums and more rounds (30,000 x 1,024 x 1,024 at
+// two rounds 83.5 us in k_gemm, 89.2 in k_gemm_resid; 65,500 x 1,024 x 1,024 at four
+// 205.7, 201.5; 65,500 x 1,024 x 4,096 490, 477).  Fitted over 524 shapes (N 512 to 4,096,
+// K 128 to 16,384, 300 to 65,500 rows): 0.7% from the best on average; 16% at most, where
+// N = 4,096 and K is at most 384 (65,500 rows: 128 x 128 tiles 529 us, 256 x 256 628).
+//
+// The bias and GELU products have no 192-wide form to choose, and keep the one line.
 template <int EPI>
 inline hipError_t launch(const uint16_t* A, const uint16_t* W, const uint16_t* bias, void* out,
                          int64_t ldc, int M, int N, int K, hipStream_t st) {
@@ -644,11 +650,15 @@ inline hipError_t launch(const uint16_t* A, const uint16_t* W, const uint16_t* b
         auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * (N / bn); };
         auto rounds = [&](int bn) { return (tiles(256, bn) + 255) / 256; };
         const int64_t t128 = tiles(128, 128), rest = t128 % 512;
-        const int64_t c128 = 70 * (t128 / 512) + (rest > 256 ? 70 : rest > 0 ? 45 : 0);
-        const int64_t c192 = N % 192 == 0 ? 78 * rounds(192) : INT64_MAX;
-        const int64_t c256 = N % 256 == 0 ? (K <= 1024 ? 116 : 100) * rounds(256) : INT64_MAX;
-        if (c256 < c128 && c256 <= c192)
+        const bool tiny = K <= 384;
+        const int64_t c128 = 68 * (t128 / 512) + (rest > 256 ? 68 : rest > 0 ? 45 : 0);
+        const int64_t c192 = N % 192 == 0 ? (tiny ? 90 : 80) * rounds(192) : INT64_MAX;
+        const int64_t c256 = N % 256 == 0 ? (tiny ? 116 : 100) * rounds(256) : INT64_MAX;
+        if (c256 < c128 && c256 <= c192) {
+            if (K <= 640 || (K <= 4096 && rounds(256) <= 3))
+                return launch_tiles<EPI, 256, 256, 4, 2>(A, W, bias, out, ldc, M, N, K, st);
             return launch_resid<2>(A, W, bias, out, ldc, M, N, K, st);
+        }
         if (c192 < c128) return launch_resid<1>(A, W, bias, out, ldc, M, N, K, st);
     } else {
         if (N % 256 == 0 && (int64_t)((M + 255) / 256) * (N / 256) >= 256)

@@ -44,3 +44,12 @@ def test_tile_choice(d, heads, ff, n):
         alone = run(cfg, fg[part], lengths[part], np.arange(part.stop - k, dtype=np.int32), T, P,
                     part.stop - k)
         assert torch.equal(alone.view(torch.int16), got[part].view(torch.int16)), k
+
+
+# 256 x 256 tiles: k_gemm's for few rounds of sums up to 4,096, k_gemm_resid's
+# for longer ones (8,192, and 4,224: 66 slabs) and for four rounds (24,700 rows, N = 2,048).
+@pytest.mark.parametrize("d,heads,ff,n", [
+    (512, 8, 4096, 32_700), (512, 8, 4224, 32_700), (1024, 16, 8192, 16_300),
+    (1024, 16, 640, 16_129), (512, 4, 384, 65_000), (2048, 32, 128, 24_700)])
+def test_whole_tiles_by_length_and_rounds(d, heads, ff, n):
+    test_tile_choice(d, heads, ff, n)
