@@ -192,7 +192,7 @@ int scone_tag(const scone_table_t* table, const int32_t* token_ids, int64_t B, i
  *             SCONE_PLACE_HBM) or host-mapped pinned memory
  *             (SCONE_PLACE_HOST).
  *  row_bytes  > 0, any width and alignment.  Rows of 16 bytes and more move
- *             in 16-byte vectors.
+ *             in vectors of up to 16 bytes.
  *  out        [n_tok, row_bytes] device output; sharing memory with `rows`
  *             or with fgram_ids gives SCONE_EINVAL.
  *

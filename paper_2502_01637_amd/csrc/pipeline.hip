@@ -56,7 +56,8 @@ __global__ __launch_bounds__(kTileThreads) void k_pipelined_units(
                             next_len, err);
         return;
     }
-    copy_units<kUnitsPerThread>(cur_ids, n_cur, blk - n_lookup_blocks, ru, rows, n_rows, out, err);
+    copy_units<kUnitsPerThread, u32x4_any>(cur_ids, n_cur, blk - n_lookup_blocks, ru, rows, n_rows,
+                                           out, err);
 }
 
 struct Step {
@@ -180,7 +181,7 @@ extern "C" int scone_embed_pipelined(const scone_table_t* table, const int32_t* 
         if (n_next > 0)
             e = launch_lookup(table, next_tokens, B, T, eff, next_ids, next_len, err, st);
         if (e == hipSuccess && n_cur > 0)
-            e = launch_gather_any(cur_ids, n_cur, rows, n_rows, row_bytes, out, err, st);
+            e = launch_gather_any(cur_ids, n_cur, rows, n_rows, row_bytes, placement, out, err, st);
     }
     return status_of(e);
 }

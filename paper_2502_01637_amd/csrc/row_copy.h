@@ -83,7 +83,7 @@ struct RowUnits {
         if (q * upr > i) --q;
         return q;
     }
-    __device__ __forceinline__ int64_t offset(int64_t c) const {  // byte of 16-byte unit c
+    __device__ __forceinline__ int64_t offset(int64_t c) const {  // byte of unaligned unit c
         const int64_t o = c * 16;
         return o <= row_bytes - 16 ? o : row_bytes - 16;
     }
@@ -107,10 +107,11 @@ inline RowUnits row_units(int64_t row_bytes, int unit_bytes = 16) {
 }
 
 // Workgroup `blk` of 256 threads copies units [blk * 256 U, (blk + 1) * 256 U) of
-// the n_tok rows of `ids`.  Lanes past the end read the last row and store
-// nothing.  An id outside [0, n_rows) (n_rows > 0) writes zeros and raises
-// SCONE_EROW.
-template <int U>
+// the n_tok rows of `ids`.  A unit is a V: u32x4_any, or a narrower aligned word
+// that divides the row (row_units with its size).  Lanes past the end read the last
+// row and store nothing.  An id outside [0, n_rows) (n_rows > 0) writes zeros and
+// raises SCONE_EROW.
+template <int U, typename V>
 __device__ __forceinline__ void copy_units(const int32_t* __restrict__ ids, int64_t n_tok,
                                            int64_t blk, const RowUnits& ru,
                                            const uint8_t* __restrict__ rows, int64_t n_rows,
@@ -120,14 +121,15 @@ __device__ __forceinline__ void copy_units(const int32_t* __restrict__ ids, int6
     const int64_t r0 = ru.div64(base);
     const uint32_t c0 = (uint32_t)(base - r0 * ru.upr);
     int64_t r[U], off[U], id[U];
-    u32x4_any v[U];
+    V v[U];
     bool in[U], ok[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const uint32_t k = c0 + u * 256 + threadIdx.x;
         const uint32_t q = ru.div(k);
         r[u] = r0 + q;
-        off[u] = ru.offset(k - q * ru.upr);
+        const uint32_t c = k - q * ru.upr;
+        off[u] = sizeof(V) == 16 ? ru.offset(c) : (int64_t)c * (int64_t)sizeof(V);
         in[u] = r[u] < n_tok;
         if (!in[u]) r[u] = n_tok - 1;
         id[u] = ids[r[u]];
@@ -135,16 +137,14 @@ __device__ __forceinline__ void copy_units(const int32_t* __restrict__ ids, int6
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         ok[u] = (id[u] >= 0) & (id[u] < n_rows);
-        v[u] = *reinterpret_cast<const u32x4_any*>(rows + (ok[u] ? id[u] : 0) * ru.row_bytes +
-                                                   off[u]);
+        v[u] = *reinterpret_cast<const V*>(rows + (ok[u] ? id[u] : 0) * ru.row_bytes + off[u]);
     }
     bool bad = false;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         if (in[u])
             __builtin_nontemporal_store(
-                ok[u] ? v[u] : u32x4_any{},
-                reinterpret_cast<u32x4_any*>(out + r[u] * ru.row_bytes + off[u]));
+                ok[u] ? v[u] : V{}, reinterpret_cast<V*>(out + r[u] * ru.row_bytes + off[u]));
         bad |= in[u] & !ok[u];
     }
     if (bad) atomicOr(err, err_bit(SCONE_EROW));
@@ -153,8 +153,8 @@ __device__ __forceinline__ void copy_units(const int32_t* __restrict__ ids, int6
 // Units per thread of copy_units.
 constexpr int kUnitsPerThread = 4;
 
-inline int64_t unit_blocks(int64_t n_tok, const RowUnits& u) {
-    return (n_tok * u.upr + 256 * kUnitsPerThread - 1) / (256 * kUnitsPerThread);
+inline int64_t unit_blocks(int64_t n_tok, const RowUnits& u, int per_thread = kUnitsPerThread) {
+    return (n_tok * u.upr + 256 * per_thread - 1) / (256 * per_thread);
 }
 
 }  // namespace scone

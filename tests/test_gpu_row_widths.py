@@ -75,3 +75,50 @@ def test_rows_past_2_gib():
     out = S.embed(table, X, 2, row)
     S.check_ok()
     assert torch.equal(out[0, 0], row[0]) and torch.equal(out[0, 1], row[0])
+
+
+# Gathered in 8-byte units (8 divides the row but 16 does not, below 4 KiB) and, over
+# PCIe, in 4-byte ones (below 2 KiB) or with one unit per thread (the fused kernel from
+# 1 KiB on): the edges of these ranges and of a workgroup's units, aligned and not.
+@pytest.mark.parametrize("row_bytes", [20, 24, 28, 40, 1000, 1016, 1020, 1028, 2040, 2044, 2052,
+                                       4088, 4104])
+@pytest.mark.parametrize("host", [False, True])
+@pytest.mark.parametrize("at", [(0, 0), (8, 8), (4, 0), (0, 4), (1, 0)])
+def test_narrow_units(row_bytes, host, at):
+    if host and at[0]:
+        pytest.skip("host rows start where they were allocated")
+    rng = np.random.default_rng(row_bytes)
+    pairs = rng.permutation(V * V)[:N]
+    fg = np.stack([pairs // V, pairs % V], 1).astype(np.int32)
+    ln = np.full(N, 2, dtype=np.int32)
+    n_rows = V + N - 3                         # the last three f-grams have no row
+    ids = (V + np.arange(N)).astype(np.int32)
+    X = rng.integers(0, V, (3, 701)).astype(np.int32)
+    want_ids, _ = oracle.OracleTable(fg, ln, ids).lookup(X, 2)
+    E = rng.integers(0, 256, (n_rows, row_bytes), dtype=np.uint8)
+    bad = want_ids >= n_rows
+    want = E[np.where(bad, 0, want_ids)]
+    want[bad] = 0
+    if host:
+        rows = S.HostRows(n_rows, (row_bytes,), torch.uint8)
+        rows.tensor().copy_(torch.from_numpy(E))
+    else:
+        store = torch.zeros(n_rows * row_bytes + 32, dtype=torch.uint8, device="cuda")
+        rows = store[at[0]:at[0] + n_rows * row_bytes].view(n_rows, row_bytes)
+        rows.copy_(dev(E))
+    table = build_gpu(fg, ln, ids)
+    cur, _ = S.lookup(table, dev(X), 2)
+    size = X.size * row_bytes
+    for call in ("gather", "embed", "pipelined"):
+        hold = torch.full((size + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+        out = hold[at[1]:at[1] + size].view(3, 701, row_bytes)
+        if call == "gather":
+            S.gather(cur, rows, out=out)
+        elif call == "embed":
+            S.embed(table, dev(X), 2, rows, out=out)
+        else:
+            S.embed_pipelined(table, dev(X), 2, torch.empty_like(cur), cur, rows, out=out)
+        assert S.check() == (S.scone.EROW if bad.any() else S.scone.OK)
+        assert np.array_equal(out.cpu().numpy(), want), call
+        edge = torch.cat([hold[:at[1]], hold[at[1] + size:]]).cpu().numpy()
+        assert (edge == 0xA5).all(), call
