@@ -115,6 +115,17 @@ int scone_build_fgram_table_in(const int32_t* fgrams, const int32_t* lengths,
                                double max_load, void* memory, int64_t memory_bytes,
                                void* stream, scone_table_t** out);
 
+/*
+ * scone_build_fgram_table_in without counting the lengths again: memory_bytes is
+ * what scone_fgram_table_bytes gave for the same lengths and load (SCONE_EINVAL for
+ * a size that it can't give).  Lengths that have changed in between may not fit:
+ * SCONE_EFULL.
+ */
+int scone_build_fgram_table_sized(const int32_t* fgrams, const int32_t* lengths,
+                                  const int32_t* ids, int64_t n, int32_t max_len,
+                                  double max_load, void* memory, int64_t memory_bytes,
+                                  void* stream, scone_table_t** out);
+
 /* *bytes (host) receives the device memory that the dictionary of these lengths
  * takes.  scratch: 256 bytes of device memory, 256-byte aligned, to count in.
  * Synchronous on `stream`. */

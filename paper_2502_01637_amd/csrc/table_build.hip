@@ -299,13 +299,12 @@ int count_slots(const int32_t* lengths, int64_t n, int32_t max_len, double max_l
 }
 
 // Fills a table of `cap` slots in `slots` and makes its handle; waits for the
-// stream.
+// stream.  `cleared`: count_slots has zeroed the control words.
 int fill_table(const int32_t* fgrams, const int32_t* lengths, const int32_t* ids, int64_t n,
-               int32_t max_len, void* slots, uint64_t cap, Control* ctl, int dev, hipStream_t st,
-               scone_table_t** out) {
+               int32_t max_len, void* slots, uint64_t cap, Control* ctl, bool cleared, int dev,
+               hipStream_t st, scone_table_t** out) {
     const int slot_bytes = slot_bytes_for(max_len);
-    if (!has_long(n, max_len))  // else count_slots has zeroed them
-        SCONE_HIP_TRY(hipMemsetAsync(ctl, 0, sizeof(Control), st));
+    if (!cleared) SCONE_HIP_TRY(hipMemsetAsync(ctl, 0, sizeof(Control), st));
     SCONE_HIP_TRY(hipMemsetAsync(slots, 0, cap * (uint64_t)slot_bytes, st));
     if (n > 0) {
         const hipError_t e =
@@ -323,6 +322,8 @@ int fill_table(const int32_t* fgrams, const int32_t* lengths, const int32_t* ids
             if (h.status & err_bit(c)) return c;
         return SCONE_EFULL;
     }
+    // More markers than the slots were sized for (the lengths have changed since).
+    if ((double)n + (double)h.markers > 0.9 * (double)cap) return SCONE_EFULL;
     scone_table* t = new (std::nothrow) scone_table();
     if (!t) return SCONE_ENOMEM;
     t->device = dev;
@@ -366,7 +367,7 @@ extern "C" int scone_build_fgram_table(const int32_t* fgrams, const int32_t* len
     }
     if (rc == SCONE_OK)
         rc = fill_table(fgrams, lengths, ids, n, max_len, slots, cap, static_cast<Control*>(ctl),
-                        dev, st, out);
+                        has_long(n, max_len), dev, st, out);
     if (rc == SCONE_OK) (*out)->owned = slots;
     else (void)hipStreamSynchronize(st);
     if (rc != SCONE_OK && slots) (void)hipFree(slots);
@@ -394,11 +395,14 @@ extern "C" int scone_fgram_table_bytes(const int32_t* lengths, int64_t n, int32_
     return rc;
 }
 
-extern "C" int scone_build_fgram_table_in(const int32_t* fgrams, const int32_t* lengths,
-                                          const int32_t* ids, int64_t n, int32_t max_len,
-                                          double max_load, void* memory, int64_t memory_bytes,
-                                          void* stream, scone_table_t** out) {
-    using namespace scone;
+namespace scone {
+namespace {
+
+// The build in the caller's memory: `sized` takes the slots from memory_bytes, which
+// scone_fgram_table_bytes has counted; else they are counted here.
+int build_in(const int32_t* fgrams, const int32_t* lengths, const int32_t* ids, int64_t n,
+             int32_t max_len, double max_load, void* memory, int64_t memory_bytes, bool sized,
+             void* stream, scone_table_t** out) {
     if (!out) return SCONE_EINVAL;
     *out = nullptr;
     int rc = build_sizes_ok(n, max_len, max_load);
@@ -414,15 +418,43 @@ extern "C" int scone_build_fgram_table_in(const int32_t* fgrams, const int32_t* 
     int dev = 0;
     SCONE_HIP_TRY(hipGetDevice(&dev));
     Control* ctl = static_cast<Control*>(memory);
+    const int64_t slot = slot_bytes_for(max_len);
     uint64_t cap = 0;
-    rc = count_slots(lengths, n, max_len, max_load, ctl, st, cap);
-    if (rc == SCONE_OK &&
-        (uint64_t)memory_bytes < cap * (uint64_t)slot_bytes_for(max_len) + kControlBytes)
-        rc = SCONE_EINVAL;
+    if (sized) {
+        cap = (uint64_t)((memory_bytes - kControlBytes) / slot);
+        if (cap < 64 || (cap & (cap - 1)) != 0 ||
+            (int64_t)cap * slot + kControlBytes != memory_bytes ||
+            (double)cap < std::ceil((double)n / max_load))
+            return SCONE_EINVAL;
+    } else {
+        rc = count_slots(lengths, n, max_len, max_load, ctl, st, cap);
+        if (rc == SCONE_OK && memory_bytes < (int64_t)cap * slot + kControlBytes)
+            rc = SCONE_EINVAL;
+    }
     if (rc == SCONE_OK)
         rc = fill_table(fgrams, lengths, ids, n, max_len,
-                        static_cast<uint8_t*>(memory) + kControlBytes, cap, ctl, dev, st, out);
+                        static_cast<uint8_t*>(memory) + kControlBytes, cap, ctl,
+                        !sized && has_long(n, max_len), dev, st, out);
     // the memory is the caller's again, whatever was queued there
     if (rc != SCONE_OK) (void)hipStreamSynchronize(st);
     return rc;
+}
+
+}  // namespace
+}  // namespace scone
+
+extern "C" int scone_build_fgram_table_in(const int32_t* fgrams, const int32_t* lengths,
+                                          const int32_t* ids, int64_t n, int32_t max_len,
+                                          double max_load, void* memory, int64_t memory_bytes,
+                                          void* stream, scone_table_t** out) {
+    return scone::build_in(fgrams, lengths, ids, n, max_len, max_load, memory, memory_bytes, false,
+                           stream, out);
+}
+
+extern "C" int scone_build_fgram_table_sized(const int32_t* fgrams, const int32_t* lengths,
+                                             const int32_t* ids, int64_t n, int32_t max_len,
+                                             double max_load, void* memory, int64_t memory_bytes,
+                                             void* stream, scone_table_t** out) {
+    return scone::build_in(fgrams, lengths, ids, n, max_len, max_load, memory, memory_bytes, true,
+                           stream, out);
 }

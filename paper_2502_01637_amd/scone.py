@@ -44,6 +44,8 @@ def _declare(L):
     L.scone_build_fgram_table_in.argtypes = [P, P, P, I64, I32, ctypes.c_double, P, I64, P,
                                              ctypes.POINTER(P)]
     L.scone_build_fgram_table_in.restype = I
+    L.scone_build_fgram_table_sized.argtypes = L.scone_build_fgram_table_in.argtypes
+    L.scone_build_fgram_table_sized.restype = I
     L.scone_fgram_table_bytes.argtypes = [P, I64, I32, ctypes.c_double, P, P,
                                           ctypes.POINTER(I64)]
     L.scone_fgram_table_bytes.restype = I
@@ -235,9 +237,9 @@ def build_fgram_table(fgrams: torch.Tensor, lengths: torch.Tensor, ids: torch.Te
                 ctypes.byref(need)) == OK:
             memory = _scratch(need.value, fgrams.device, stream)
         if memory is not None:
-            rc = lib().scone_build_fgram_table_in(
+            rc = lib().scone_build_fgram_table_sized(
                 _ptr(fgrams), _ptr(lengths), _ptr(ids), n, K, float(max_load),
-                memory.data_ptr(), memory.numel(), st, ctypes.byref(h))
+                memory.data_ptr(), need.value, st, ctypes.byref(h))
         else:  # arguments that the library refuses, or no memory left for torch
             rc = lib().scone_build_fgram_table(_ptr(fgrams), _ptr(lengths), _ptr(ids), n, K,
                                                float(max_load), st, ctypes.byref(h))

@@ -96,6 +96,26 @@ def test_table_sizes_leave_nothing_queued(stub, max_len, n):
         assert out[1] == "log=" or out[1].endswith("S"), out
 
 
+@pytest.mark.parametrize("max_len,waits", [(3, 1), (5, 2)])
+def test_lengths_are_counted_once(stub, max_len, waits):
+    """The sizes and then the build, as the binding calls them: the host waits for
+    the count of the longer lengths, where there can be any, and for the table."""
+    slot = 16 if max_len <= 5 else 32
+    out = run(stub, f"""
+        b, h = I64(), P()
+        a = lambda k: P(A + (k << 24))
+        r0 = L.scone_fgram_table_bytes(a(0), I64(1000), I32({max_len}), D(0.25), a(1), None,
+                                       ctypes.byref(b))
+        rc = lambda nbytes: L.scone_build_fgram_table_sized(
+            a(2), a(0), a(3), I64(1000), I32({max_len}), D(0.25), a(4), I64(nbytes), None,
+            ctypes.byref(h))
+        r1 = rc(b.value)
+        print(r0, r1, b.value, log().decode().count("S"),
+              *[rc(k) for k in (0, 256, b.value - 1, b.value + {slot}, b.value // 2 + 128)])
+    """)
+    assert out == ["0", "0", str(4096 * slot + 256), str(waits)] + ["1"] * 5
+
+
 def test_discovery_tells_its_two_data_errors_apart(stub):
     """The status word's bits: a bad token, regions that disagree, and both."""
     for bits, want in [(1 << 8, "8"), (1 << 5, "5"), (1 << 8 | 1 << 5, "8")]:
