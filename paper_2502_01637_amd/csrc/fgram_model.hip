@@ -474,7 +474,7 @@ int run_model(const int32_t* fgrams, const int32_t* lengths, const int32_t* row_
     const ChunkFn fn = chunk_fn(d);
     if (!fn) return SCONE_EINVAL;
     const ModelLayout lay = model_layout(n, max_len, d, d_ff);
-    const tree::Builder tb{fgrams, lengths, n, max_len, vocab, ws, lay.tree, st};
+    const tree::Builder tb{fgrams, lengths, n, max_len, vocab, ws, lay.tree, n_layers == 0, st};
     std::vector<Chunk> chunks;
     unsigned bits = 0;
     const int rc = tb.build(chunks, bits);

@@ -9,13 +9,15 @@
 // inside one chunk.
 //
 //   k_check                 lengths and tokens in range
-//   k_rank + k_place        the sort of a small list: each f-gram's rank is the
+//   k_rank + k_place        the sort of a short list: each f-gram's rank is the
 //                           number of f-grams below it
-//   k_radix_* + scan        the sort of a larger one: stable 8-bit passes over
+//   k_radix_* + scan        the sort of a longer one: stable 8-bit passes over
 //                           the tokens but the last, from the last byte to the first
 //   k_share + scan          share and the inner nodes added before each f-gram
 //   k_chunks                chunk limits, read back by the host
 //   k_nodes (per chunk)     one record per node
+//   k_last_nodes            instead of all but the check, where the model has no layers:
+//                           no state but an f-gram's last is read
 //
 // The sort leaves out the last of max_len tokens, so full-length f-grams with
 // one prefix are in any order; only nodes above the last depth are looked up.
@@ -35,10 +37,12 @@ constexpr int kThreads = 256;
 // half and of a quarter this size were 0% and 2% slower.
 constexpr int64_t kChunkRows = 65536;
 
-// Up to here the sort counts ranks, n * n comparisons in two launches (13 us at
-// 3,000 f-grams); the radix passes need five launches for each byte of max_len
-// - 1 tokens, 40 for K = 5 (264 us for the 20 of 1M f-grams with K = 3).
-constexpr int64_t kRankMax = 8192;
+// The sort counts ranks, n * n comparisons in two launches, while those are at most
+// this many per radix pass (five launches each, one pass for each byte of max_len
+// - 1 tokens).  Whole calls of a model with no layers by ranks and by passes: K = 2
+// with one pass, 8,000 f-grams 152, 152 us; K = 3 with four, 24,000 291, 316 us, 32,000
+// 423, 364; K = 7 with twelve, 8,000 180, 529 us, 32,000 679, 770, 48,000 1,207, 865.
+constexpr int64_t kRankPerPass = 100000000;
 
 // One node: its token, its position in the f-gram and the rows of its
 // ancestors, oldest first (up[0 .. pos)).
@@ -481,6 +485,24 @@ __global__ __launch_bounds__(kThreads) void k_nodes(const int32_t* __restrict__ 
     }
 }
 
+// The last nodes of a chunk's f-grams in input order, which is written to `order`:
+// all that a model with no layers reads.
+__global__ __launch_bounds__(kThreads) void k_last_nodes(const int32_t* __restrict__ fgrams,
+                                                         const int32_t* __restrict__ lengths,
+                                                         int max_len, int64_t vocab, Chunk c,
+                                                         int32_t* __restrict__ order,
+                                                         Node* __restrict__ nodes) {
+    const int64_t f = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (f >= c.n_f) return;
+    const int64_t g = c.first + f;
+    const int len = len_of(lengths, g, max_len);
+    Node nd{};
+    nd.pos = len - 1;
+    nd.tok = (int32_t)(key_at(fgrams + g * max_len, len, len - 1, vocab) - 1u);
+    nodes[f] = nd;
+    order[g] = (int32_t)g;
+}
+
 // ------------------------------------------------------------------ host ----
 
 struct Layout {
@@ -525,6 +547,7 @@ struct Builder {
     int64_t vocab;
     uint8_t* ws;
     Layout l;
+    bool flat;  // no tree: the f-grams' last nodes alone, in input order
     hipStream_t st;
 
     template <typename T>
@@ -532,7 +555,9 @@ struct Builder {
         return reinterpret_cast<T*>(ws + off);
     }
     unsigned* status() const { return at<unsigned>(l.ctl); }
-    const int32_t* order() const { return at<int32_t>(radix_passes() % 2 ? l.order_b : l.order_a); }
+    const int32_t* order() const {
+        return at<int32_t>(!flat && radix_passes() % 2 ? l.order_b : l.order_a);
+    }
     Node* nodes() const { return at<Node>(l.nodes); }
 
     // Bytes of the largest key value, `vocab` (a token plus one).
@@ -542,7 +567,10 @@ struct Builder {
         return b;
     }
     // Radix passes; 0 where the rank sort is used.  Pass 0 writes order_b.
-    int radix_passes() const { return n <= kRankMax ? 0 : (max_len - 1) * key_bytes(); }
+    int radix_passes() const {
+        const int passes = (max_len - 1) * key_bytes();
+        return n * n <= kRankPerPass * passes ? 0 : passes;
+    }
 
     hipError_t sort() const {
         const unsigned g_n = (unsigned)((n + kThreads - 1) / kThreads);
@@ -577,7 +605,7 @@ struct Builder {
         return hipGetLastError();
     }
 
-    // Sorts the f-grams and finds the chunks; waits for the stream.  `bits` gets
+    // Sorts the f-grams (unless flat) and finds the chunks; waits for the stream.  `bits` gets
     // the data errors found (err_bit of SCONE_ELEN and SCONE_ETOKEN).
     int build(std::vector<Chunk>& chunks, unsigned& bits) const {
         const unsigned g_n = (unsigned)((n + kThreads - 1) / kThreads);
@@ -586,6 +614,15 @@ struct Builder {
         hipLaunchKernelGGL(k_check, dim3(g_n), dim3(kThreads), 0, st, fgrams, lengths, n, max_len,
                            vocab, status());
         SCONE_HIP_TRY(hipGetLastError());
+        if (flat) {
+            SCONE_HIP_TRY(hipMemcpyAsync(&bits, status(), sizeof(bits), hipMemcpyDeviceToHost, st));
+            SCONE_HIP_TRY(hipStreamSynchronize(st));
+            for (int64_t s = 0; s < n; s += l.max_rows) {
+                const int64_t n_f = n - s < l.max_rows ? n - s : l.max_rows;
+                chunks.push_back(Chunk{s, 0, n_f, n_f, 0});
+            }
+            return SCONE_OK;
+        }
         SCONE_HIP_TRY(sort());
         hipLaunchKernelGGL(k_share, dim3(g_n1), dim3(kThreads), 0, st, fgrams, lengths, n, max_len,
                            vocab, order(), at<uint8_t>(l.share), at<uint8_t>(l.adds));
@@ -615,6 +652,12 @@ struct Builder {
 
     // Writes the nodes of one of build's chunks.
     hipError_t fill_nodes(const Chunk& c) const {
+        if (flat) {
+            hipLaunchKernelGGL(k_last_nodes, dim3((unsigned)((c.n_f + kThreads - 1) / kThreads)),
+                               dim3(kThreads), 0, st, fgrams, lengths, max_len, vocab, c,
+                               at<int32_t>(l.order_a), nodes());
+            return hipGetLastError();
+        }
         hipLaunchKernelGGL(k_nodes, dim3((unsigned)((c.n_f + kThreads - 1) / kThreads)),
                            dim3(kThreads), 0, st, fgrams, lengths, max_len, vocab, order(),
                            at<uint8_t>(l.share), at<int64_t>(l.inner), c, nodes());

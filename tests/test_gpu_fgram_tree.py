@@ -17,7 +17,7 @@ from gpu_util import dev
 from test_gpu_fgram_model import as_f64, assert_close, bf16_dev, random_fgrams, run
 
 # (n, vocabulary, K): one f-gram; prefixes that nearly all share, duplicates
-# among them; the largest rank sort and the smallest radix sort; key values of
+# among them; rank sorts and radix sorts; key values of
 # one, two and three bytes; one prefix group over several chunks; many chunks
 CASES = [(1, 5, 7), (3000, 2, 7), (8192, 300, 5), (8193, 300, 5), (9000, 255, 3),
          (9000, 256, 6), (9000, 65535, 3), (9000, 65536, 3), (9000, 70000, 4),
@@ -52,6 +52,43 @@ def test_shared_prefixes(case):
                 len(pick))
     assert torch.equal(alone.view(torch.int16),
                        got[torch.from_numpy(ids[pick].astype(np.int64)).cuda()].view(torch.int16))
+
+
+
+# n * n = 1e8 per radix pass is the most that ranks are counted for: one, four
+# (two bytes of a key of two tokens) and eighteen passes.
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [(10_000, 200, 2), (10_001, 200, 2), (20_000, 300, 3),
+                                  (20_001, 300, 3), (42_426, 65_536, 7), (42_427, 65_536, 7)],
+                         ids=pytest_id)
+def test_both_sorts_at_their_line(case):
+    test_shared_prefixes(case)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 9000, 70_001])
+def test_no_layers(n):
+    """Rows of a model with no layers: LNf(T + P) of the last token alone, in one
+    chunk and in several; a bad length writes nothing."""
+    K, V = 5, 65_535
+    cfg = ModelConfig(512, 8, 128, 0, K)
+    rng = np.random.default_rng(n)
+    P, T = make_params(cfg, seed=1), make_token_rows(V, cfg.d, seed=2)
+    fg, lengths = random_fgrams(rng, V, n, K)
+    fg[:, 0] = 7
+    ids = rng.permutation(n).astype(np.int32)
+    got = run(cfg, fg, lengths, ids, T, P, n)
+    pick = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, 300)]))
+    ref = orc.forward(fg[pick], lengths[pick], bf16_bits_to_f64(T),
+                      {k: bf16_bits_to_f64(v) for k, v in P.items()}, 0, 8)
+    assert_close(as_f64(got[torch.from_numpy(ids[pick].astype(np.int64)).cuda()]), ref, 0)
+    assert (got.float().abs().sum(1) > 0).all()
+    lengths[n // 2] = K + 1
+    model = S.FgramModel(P, cfg.d, cfg.n_heads, cfg.d_ff, 0, K)
+    rows = torch.zeros((n, cfg.d), dtype=torch.bfloat16, device="cuda")
+    with pytest.raises(S.SconeError) as e:
+        S.precompute_fgram_rows(model, dev(fg), dev(lengths), dev(ids), bf16_dev(T), rows)
+    assert e.value.code == S.scone.ELEN and not rows.any()
 
 
 @pytest.mark.gpu

@@ -148,3 +148,20 @@ def test_discovery_reports_a_failed_last_wait(stub):
         """)
         assert out[0] == want and out[1] == ("20" if want == "0" else "0"), out
         assert out[2].endswith("DSUKS"), out
+
+
+@pytest.mark.parametrize("n,layers,most", [(1, 0, 4), (8193, 0, 4), (8193, 1, 18),
+                                           (20_000, 1, 40)])
+def test_launches_of_small_precomputes(stub, n, layers, most):
+    """K = 7: no tree without layers, and no radix passes (five launches for each
+    of twelve) where counting ranks is faster."""
+    out = run(stub, f"""
+        a = lambda k: P(A + (k << 34))
+        L.scone_fgram_model_workspace.restype = I64
+        need = L.scone_fgram_model_workspace(I64({n}), 7, 512, 8, 128)
+        rc = L.scone_fgram_model_forward_in(a(0), a(1), a(2), I64({n}), 7, a(3), I64(50257), a(4),
+                                            512, 8, 128, {layers}, a(5), I64({n}), a(6), I64(need),
+                                            None)
+        print(rc, log().decode().count("K"))
+    """)
+    assert out[0] == "0" and int(out[1]) <= most, out
