@@ -8,6 +8,8 @@
 // chunk's first f-gram adds its whole path again, so that every path lies
 // inside one chunk.
 //
+//   k_short_list            all of the following up to the chunk limits, for fewer than
+//                           256 f-grams
 //   k_check                 lengths and tokens in range
 //   k_rank + k_place        the sort of a short list: each f-gram's rank is the
 //                           number of f-grams below it
@@ -23,6 +25,7 @@
 // one prefix are in any order; only nodes above the last depth are looked up.
 #pragma once
 
+#include <cstring>
 #include <vector>
 
 #include "scone_internal.h"
@@ -79,28 +82,51 @@ __device__ __forceinline__ int len_of(const int32_t* __restrict__ lengths, int64
     return len < 2 ? 2 : len > max_len ? max_len : len;
 }
 
+// err_bit of SCONE_ELEN and SCONE_ETOKEN, as f-gram g has them.
+__device__ __forceinline__ unsigned data_errors(const int32_t* __restrict__ fgrams,
+                                                const int32_t* __restrict__ lengths, int64_t g,
+                                                int max_len, int64_t vocab) {
+    const int len = len_of(lengths, g, max_len);
+    unsigned bad = lengths[g] != len ? err_bit(SCONE_ELEN) : 0u;
+    for (int i = 0; i < len; ++i) {
+        const int32_t t = fgrams[g * max_len + i];
+        if (t < 0 || (int64_t)t >= vocab) bad |= err_bit(SCONE_ETOKEN);
+    }
+    return bad;
+}
+
 __global__ __launch_bounds__(kThreads) void k_check(const int32_t* __restrict__ fgrams,
                                                     const int32_t* __restrict__ lengths,
                                                     int64_t n, int max_len, int64_t vocab,
                                                     unsigned* __restrict__ status) {
     const int64_t g = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (g >= n) return;
-    const int32_t raw = lengths[g];
-    const int len = len_of(lengths, g, max_len);
-    unsigned bad = raw != len ? err_bit(SCONE_ELEN) : 0u;
-    for (int i = 0; i < len; ++i) {
-        const int32_t t = fgrams[g * max_len + i];
-        if (t < 0 || (int64_t)t >= vocab) bad |= err_bit(SCONE_ETOKEN);
-    }
+    const unsigned bad = data_errors(fgrams, lengths, g, max_len, vocab);
     if (bad) atomicOr(status, bad);
 }
 
 // ------------------------------------------------------------- rank sort ----
+
+// The sort key of f-gram g: max_len - 1 tokens, paired into 64 bits (NK words).
+template <int NK>
+__device__ __forceinline__ void sort_key(const int32_t* __restrict__ fgrams,
+                                         const int32_t* __restrict__ lengths, int64_t g,
+                                         int max_len, int64_t vocab, uint64_t (&k)[NK]) {
+    const int len = len_of(lengths, g, max_len);
+#pragma unroll
+    for (int w = 0; w < NK; ++w) {
+        const uint64_t hi = 2 * w < max_len - 1 ? key_at(fgrams + g * max_len, len, 2 * w, vocab) : 0;
+        const uint64_t lo =
+            2 * w + 1 < max_len - 1 ? key_at(fgrams + g * max_len, len, 2 * w + 1, vocab) : 0;
+        k[w] = (hi << 32) | lo;
+    }
+}
+
 // Workgroup (x, y) counts, for each of 256 f-grams, how many of kRankTile others
 // come before it (equal keys in input order).
 constexpr int kRankTile = 64;
 
-template <int NK>  // key words: max_len - 1 tokens, paired into 64 bits
+template <int NK>
 __global__ __launch_bounds__(kThreads) void k_rank(const int32_t* __restrict__ fgrams,
                                                    const int32_t* __restrict__ lengths, int64_t n,
                                                    int max_len, int64_t vocab,
@@ -108,21 +134,11 @@ __global__ __launch_bounds__(kThreads) void k_rank(const int32_t* __restrict__ f
     __shared__ uint64_t s_key[kRankTile][NK];
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     const int64_t j0 = (int64_t)blockIdx.y * kRankTile;
-    auto load = [&](int64_t g, uint64_t (&k)[NK]) {
-        const int len = len_of(lengths, g, max_len);
-#pragma unroll
-        for (int w = 0; w < NK; ++w) {
-            const uint64_t hi = 2 * w < max_len - 1 ? key_at(fgrams + g * max_len, len, 2 * w, vocab) : 0;
-            const uint64_t lo =
-                2 * w + 1 < max_len - 1 ? key_at(fgrams + g * max_len, len, 2 * w + 1, vocab) : 0;
-            k[w] = (hi << 32) | lo;
-        }
-    };
     uint64_t mine[NK] = {};
-    if (i < n) load(i, mine);
+    if (i < n) sort_key(fgrams, lengths, i, max_len, vocab, mine);
     if (threadIdx.x < kRankTile && j0 + threadIdx.x < n) {
         uint64_t k[NK];
-        load(j0 + threadIdx.x, k);
+        sort_key(fgrams, lengths, j0 + threadIdx.x, max_len, vocab, k);
 #pragma unroll
         for (int w = 0; w < NK; ++w) s_key[threadIdx.x][w] = k[w];
     }
@@ -328,6 +344,19 @@ inline hipError_t scan(const In* in, int64_t n, T* sums, T* out, hipStream_t st)
 
 // ------------------------------------------------------------------ tree ----
 
+// The depths that f-gram g shares with f-gram p, its neighbour in sorted order.
+__device__ __forceinline__ int shared_depths(const int32_t* __restrict__ fgrams,
+                                             const int32_t* __restrict__ lengths, int max_len,
+                                             int64_t vocab, int64_t g, int64_t p) {
+    const int len = len_of(lengths, g, max_len), plen = len_of(lengths, p, max_len);
+    int c = 0;
+    while (c < len - 1 && c < plen &&
+           key_at(fgrams + g * max_len, len, c, vocab) ==
+               key_at(fgrams + p * max_len, plen, c, vocab))
+        ++c;
+    return c;
+}
+
 // share[s] and the inner nodes that f-gram s adds, for s <= n (the last one is
 // an end mark that adds none, so that its scanned value is the total).
 __global__ __launch_bounds__(kThreads) void k_share(const int32_t* __restrict__ fgrams,
@@ -341,16 +370,8 @@ __global__ __launch_bounds__(kThreads) void k_share(const int32_t* __restrict__ 
     int c = 0, add = 0;
     if (s < n) {
         const int64_t g = order[s];
-        const int len = len_of(lengths, g, max_len);
-        if (s > 0) {
-            const int64_t p = order[s - 1];
-            const int plen = len_of(lengths, p, max_len);
-            while (c < len - 1 && c < plen &&
-                   key_at(fgrams + g * max_len, len, c, vocab) ==
-                       key_at(fgrams + p * max_len, plen, c, vocab))
-                ++c;
-        }
-        add = len - 1 - c;
+        if (s > 0) c = shared_depths(fgrams, lengths, max_len, vocab, g, order[s - 1]);
+        add = len_of(lengths, g, max_len) - 1 - c;
     }
     share[s] = (uint8_t)c;
     adds[s] = (uint8_t)add;
@@ -382,6 +403,63 @@ __global__ __launch_bounds__(kThreads) void k_chunks(const int64_t* __restrict__
         else lo = mid + 1;
     }
     limits[k] = Limit{lo, inner[lo], (int64_t)share[lo]};
+}
+
+// Everything up to the chunk limits for fewer than kThreads f-grams, in one
+// workgroup: such a list is one chunk, and the ten operations that this replaces
+// are launches one after another (one f-gram through one layer of d = 512 165-174 us,
+// now 119-124).
+template <int NK>
+__global__ __launch_bounds__(kThreads) void k_short_list(
+    const int32_t* __restrict__ fgrams, const int32_t* __restrict__ lengths, int n, int max_len,
+    int64_t vocab, int32_t* __restrict__ order, uint8_t* __restrict__ share,
+    int64_t* __restrict__ inner, Limit* __restrict__ limits, unsigned* __restrict__ status) {
+    __shared__ uint64_t s_key[kThreads][NK];
+    __shared__ int s_order[kThreads], s_sum[kThreads / 64];
+    __shared__ unsigned s_bad;
+    const int t = threadIdx.x;
+    if (t == 0) s_bad = 0;
+    uint64_t mine[NK] = {};
+    unsigned bad = 0;
+    if (t < n) {
+        sort_key(fgrams, lengths, t, max_len, vocab, mine);
+        bad = data_errors(fgrams, lengths, t, max_len, vocab);
+    }
+#pragma unroll
+    for (int w = 0; w < NK; ++w) s_key[t][w] = mine[w];
+    __syncthreads();
+    if (bad) atomicOr(&s_bad, bad);
+    int rank = 0;
+    for (int j = 0; j < n; ++j) {
+        bool lt = false, eq = true;
+#pragma unroll
+        for (int w = 0; w < NK; ++w) {
+            const uint64_t k = s_key[j][w];
+            lt |= eq & (k < mine[w]);
+            eq &= k == mine[w];
+        }
+        rank += lt || (eq && j < t) ? 1 : 0;
+    }
+    if (t < n) s_order[rank] = t;
+    __syncthreads();
+    int c = 0, add = 0;
+    if (t < n) {
+        const int g = s_order[t];
+        if (t > 0) c = shared_depths(fgrams, lengths, max_len, vocab, g, s_order[t - 1]);
+        add = len_of(lengths, g, max_len) - 1 - c;
+        order[t] = g;
+    }
+    int total;
+    const int at = block_exclusive(add, s_sum, total);
+    if (t <= n) {
+        share[t] = (uint8_t)c;
+        inner[t] = at;
+    }
+    if (t == 0) {
+        limits[0] = Limit{0, 0, 0};
+        limits[1] = Limit{n, total, 0};
+        *status = s_bad;
+    }
 }
 
 // The nodes of one chunk.  A thread owns one f-gram; the node at depth i of its
@@ -605,38 +683,60 @@ struct Builder {
         return hipGetLastError();
     }
 
-    // Sorts the f-grams (unless flat) and finds the chunks; waits for the stream.  `bits` gets
-    // the data errors found (err_bit of SCONE_ELEN and SCONE_ETOKEN).
-    int build(std::vector<Chunk>& chunks, unsigned& bits) const {
+    // The tree up to the chunk limits, on the device.
+    hipError_t find_chunks() const {
         const unsigned g_n = (unsigned)((n + kThreads - 1) / kThreads);
         const unsigned g_n1 = (unsigned)((n + kThreads) / kThreads);
-        SCONE_HIP_TRY(hipMemsetAsync(status(), 0, sizeof(unsigned), st));
-        hipLaunchKernelGGL(k_check, dim3(g_n), dim3(kThreads), 0, st, fgrams, lengths, n, max_len,
-                           vocab, status());
-        SCONE_HIP_TRY(hipGetLastError());
+        const dim3 block(kThreads);
+        if (!flat && n < kThreads) {
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(1), block, 0, st, fgrams, lengths, (int)n, max_len,
+                                   vocab, at<int32_t>(l.order_a), at<uint8_t>(l.share),
+                                   at<int64_t>(l.inner), at<Limit>(l.limits), status());
+            };
+            switch (max_len / 2) {  // words of max_len - 1 tokens, two to a word
+                case 1: launch(k_short_list<1>); break;
+                case 2: launch(k_short_list<2>); break;
+                default: launch(k_short_list<3>); break;
+            }
+            return hipGetLastError();
+        }
+        hipError_t e = hipMemsetAsync(status(), 0, sizeof(unsigned), st);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_check, dim3(g_n), block, 0, st, fgrams, lengths, n, max_len, vocab,
+                           status());
+        if (flat) return hipGetLastError();
+        e = sort();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_share, dim3(g_n1), block, 0, st, fgrams, lengths, n, max_len, vocab,
+                           order(), at<uint8_t>(l.share), at<uint8_t>(l.adds));
+        e = scan(at<uint8_t>(l.adds), n + 1, at<int64_t>(l.sums), at<int64_t>(l.inner), st);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_chunks, dim3((unsigned)((l.n_limits + kThreads - 1) / kThreads)),
+                           block, 0, st, at<int64_t>(l.inner), n, at<uint8_t>(l.share), max_len,
+                           l.n_limits, at<Limit>(l.limits));
+        return hipGetLastError();
+    }
+
+    // Sorts the f-grams (unless flat) and finds the chunks; waits for the stream.
+    // `bits` gets the data errors found (err_bit of SCONE_ELEN and SCONE_ETOKEN).
+    int build(std::vector<Chunk>& chunks, unsigned& bits) const {
+        SCONE_HIP_TRY(find_chunks());
+        // the status word and, right behind its 256 bytes, the limits in one copy
+        std::vector<Limit> lim(flat ? 0 : (size_t)l.n_limits);
+        std::vector<uint8_t> back((l.limits - l.ctl) + lim.size() * sizeof(Limit));
+        SCONE_HIP_TRY(hipMemcpyAsync(back.data(), ws + l.ctl, back.size(), hipMemcpyDeviceToHost,
+                                     st));
+        SCONE_HIP_TRY(hipStreamSynchronize(st));
+        std::memcpy(&bits, back.data(), sizeof(bits));
         if (flat) {
-            SCONE_HIP_TRY(hipMemcpyAsync(&bits, status(), sizeof(bits), hipMemcpyDeviceToHost, st));
-            SCONE_HIP_TRY(hipStreamSynchronize(st));
             for (int64_t s = 0; s < n; s += l.max_rows) {
                 const int64_t n_f = n - s < l.max_rows ? n - s : l.max_rows;
                 chunks.push_back(Chunk{s, 0, n_f, n_f, 0});
             }
             return SCONE_OK;
         }
-        SCONE_HIP_TRY(sort());
-        hipLaunchKernelGGL(k_share, dim3(g_n1), dim3(kThreads), 0, st, fgrams, lengths, n, max_len,
-                           vocab, order(), at<uint8_t>(l.share), at<uint8_t>(l.adds));
-        SCONE_HIP_TRY(scan(at<uint8_t>(l.adds), n + 1, at<int64_t>(l.sums), at<int64_t>(l.inner),
-                           st));
-        hipLaunchKernelGGL(k_chunks, dim3((unsigned)((l.n_limits + kThreads - 1) / kThreads)),
-                           dim3(kThreads), 0, st, at<int64_t>(l.inner), n, at<uint8_t>(l.share),
-                           max_len, l.n_limits, at<Limit>(l.limits));
-        SCONE_HIP_TRY(hipGetLastError());
-        std::vector<Limit> lim((size_t)l.n_limits);
-        SCONE_HIP_TRY(hipMemcpyAsync(&bits, status(), sizeof(bits), hipMemcpyDeviceToHost, st));
-        SCONE_HIP_TRY(hipMemcpyAsync(lim.data(), at<Limit>(l.limits), lim.size() * sizeof(Limit),
-                                     hipMemcpyDeviceToHost, st));
-        SCONE_HIP_TRY(hipStreamSynchronize(st));
+        std::memcpy(lim.data(), back.data() + (l.limits - l.ctl), lim.size() * sizeof(Limit));
         for (size_t k = 0; k + 1 < lim.size() && lim[k].first < n; ++k) {
             Chunk c;
             c.first = lim[k].first;

@@ -65,6 +65,37 @@ def test_both_sorts_at_their_line(case):
     test_shared_prefixes(case)
 
 
+# Fewer than 256 f-grams are sorted and linked by one workgroup.
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [(1, 5, 2), (2, 1, 2), (3, 2, 3), (64, 3, 4), (65, 300, 5),
+                                  (254, 70_000, 6), (255, 2, 7), (256, 2, 7)], ids=pytest_id)
+def test_short_lists(case):
+    test_shared_prefixes(case)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 255, 256])
+def test_errors_of_short_lists(n):
+    cfg = ModelConfig(512, 8, 128, 1, 3)
+    rng = np.random.default_rng(n)
+    P, T = make_params(cfg, seed=1), make_token_rows(50, cfg.d, seed=2)
+    model = S.FgramModel(P, cfg.d, cfg.n_heads, cfg.d_ff, 1, 3)
+    for what, code in [("length", S.scone.ELEN), ("token", S.scone.ETOKEN), ("row", S.scone.EROW)]:
+        fg, lengths = random_fgrams(rng, 50, n, 3)
+        ids = np.arange(n, dtype=np.int32)
+        if what == "length":
+            lengths[-1], fg[0, 0] = 1, 50          # the length comes first
+        elif what == "token":
+            fg[-1, 1] = -1
+        else:
+            ids[0] = n
+        rows = torch.zeros((n, cfg.d), dtype=torch.bfloat16, device="cuda")
+        with pytest.raises(S.SconeError) as e:
+            S.precompute_fgram_rows(model, dev(fg), dev(lengths), dev(ids), bf16_dev(T), rows)
+        assert e.value.code == code
+        assert what != "length" or not rows.any()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("n", [1, 9000, 70_001])
 def test_no_layers(n):

@@ -150,11 +150,11 @@ def test_discovery_reports_a_failed_last_wait(stub):
         assert out[2].endswith("DSUKS"), out
 
 
-@pytest.mark.parametrize("n,layers,most", [(1, 0, 4), (8193, 0, 4), (8193, 1, 18),
-                                           (20_000, 1, 40)])
+@pytest.mark.parametrize("n,layers,most", [(1, 0, 4), (8193, 0, 4), (1, 1, 11), (255, 1, 11),
+                                           (8193, 1, 18), (20_000, 1, 40)])
 def test_launches_of_small_precomputes(stub, n, layers, most):
-    """K = 7: no tree without layers, and no radix passes (five launches for each
-    of twelve) where counting ranks is faster."""
+    """K = 7: no tree without layers, one launch for the tree of a short list, and no
+    radix passes (five launches for each of twelve) where counting ranks is faster."""
     out = run(stub, f"""
         a = lambda k: P(A + (k << 34))
         L.scone_fgram_model_workspace.restype = I64
