@@ -82,11 +82,10 @@ def test_rows_past_2_gib():
 # 1 KiB on): the edges of these ranges and of a workgroup's units, aligned and not.
 @pytest.mark.parametrize("row_bytes", [20, 24, 28, 40, 1000, 1016, 1020, 1028, 2040, 2044, 2052,
                                        4088, 4104])
-@pytest.mark.parametrize("host", [False, True])
-@pytest.mark.parametrize("at", [(0, 0), (8, 8), (4, 0), (0, 4), (1, 0)])
+@pytest.mark.parametrize("host,at", [(False, (0, 0)), (False, (8, 8)), (False, (4, 0)),
+                                     (False, (0, 4)), (False, (1, 0)), (True, (0, 0)),
+                                     (True, (0, 4))])
 def test_narrow_units(row_bytes, host, at):
-    if host and at[0]:
-        pytest.skip("host rows start where they were allocated")
     rng = np.random.default_rng(row_bytes)
     pairs = rng.permutation(V * V)[:N]
     fg = np.stack([pairs // V, pairs % V], 1).astype(np.int32)
