@@ -1179,7 +1179,7 @@ def run_precompute(args, cfg):
 # kernels in dispatch order against that plan, so each figure is taken over
 # the timed dispatches of one phase only.
 
-BUILD_KERNELS = ("k_count_long", "k_insert", "k_verify", "k_mark", "k_count_used")
+BUILD_KERNELS = ("k_count_long", "k_insert", "k_verify", "k_mark")
 
 
 def _short(name: str) -> str:
@@ -1416,7 +1416,8 @@ def reduce_precompute(trace_csv, bench_json, pmc_csv, out_md, trace_cmd, pmc_cmd
     L += ["", "Reduced with `python bench.py --reduce-precompute <trace csv> --bench-json "
           "<bench stdout> [--pmc <counter csv>] --out <this file>`.\n",
           "Sources (sha1): " + ", ".join(f"{x} {source_sha(x)}" for x in
-                                         ("fgram_model.hip", "gemm_bf16.h")) + ".\n",
+                                         ("fgram_model.hip", "fgram_tree.h", "gemm_bf16.h"))
+          + ".\n",
           "Per-kernel durations (ns), one line per (kernel, grid):\n", "```"]
     for (name, grid), rs in sorted(by.items(), key=lambda kv: -sum(x["ns"] for x in kv[1])):
         v = [x["ns"] for x in rs]
