@@ -417,7 +417,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(const uint16_t* __restr
 // 8,192); it is here because its accumulators and fragments leave registers for the
 // residual values, whose loads are in flight two quadrants ahead, and because a
 // width of 192 fills the chip where 256 does not: 65,459 x 1,024 x 4,096 492 -> 479
-// us, 6,800 x 1,536 x 6,144 156 (128 x 128 tiles) -> 128 us, x 1,536 52 -> 46 us.
+// us, 6,800 x 1,536 x 6,144 153 (128 x 128 tiles) -> 128 us, x 1,536 52 -> 45 us.
 template <int X1>
 __global__ __launch_bounds__(512) void k_gemm_resid(const uint16_t* __restrict__ A,
                                                     const uint16_t* __restrict__ W,

@@ -59,8 +59,9 @@ __host__ __device__ constexpr int wave_row_units(int64_t row_bytes) {
 // multiplication.  Before, the gather took 64-bit divisions and units as narrow as
 // the alignment, and the fused kernel single bytes: 131K rows of 2002 bytes took
 // 166 us to gather (now 84, 6.3 TB/s), of 4100 bytes 198 us (now 162), and 26K
-// rows of 3 KiB 101 us in the fused kernel (now 26).  Widths that were aligned
-// before moved by less than 7%, all of them down.
+// rows of 3 KiB 95 us in the fused kernel (now 27.5).  Widths that 16 divides moved
+// by less than 7%, all of them down; the gather's widths that 8 divides and 16
+// doesn't were 5% slower and have units of their own.
 
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 
