@@ -17,8 +17,8 @@ from gpu_util import dev
 from test_gpu_fgram_model import as_f64, assert_close, bf16_dev, random_fgrams, run
 
 # (n, vocabulary, K): one f-gram; prefixes that nearly all share, duplicates
-# among them; rank sorts and radix sorts; key values of
-# one, two and three bytes; one prefix group over several chunks; many chunks
+# among them; rank sorts with key values of one, two and three bytes; radix sorts:
+# one prefix group over several chunks; many chunks
 CASES = [(1, 5, 7), (3000, 2, 7), (8192, 300, 5), (8193, 300, 5), (9000, 255, 3),
          (9000, 256, 6), (9000, 65535, 3), (9000, 65536, 3), (9000, 70000, 4),
          (150_000, 1, 2), (70_001, 30, 4), (120_000, 3000, 3)]
@@ -56,11 +56,13 @@ def test_shared_prefixes(case):
 
 
 # n * n = 1e8 per radix pass is the most that ranks are counted for: one, four
-# (two bytes of a key of two tokens) and eighteen passes.
+# (two bytes of a key of two tokens) and eighteen passes; then radix passes over
+# the largest and smallest key values of one, two and three bytes.
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", [(10_000, 200, 2), (10_001, 200, 2), (20_000, 300, 3),
-                                  (20_001, 300, 3), (42_426, 65_536, 7), (42_427, 65_536, 7)],
-                         ids=pytest_id)
+                                  (20_001, 300, 3), (42_426, 65_536, 7), (42_427, 65_536, 7),
+                                  (14_143, 255, 3), (20_001, 256, 3), (20_001, 65_535, 3),
+                                  (24_495, 65_536, 3)], ids=pytest_id)
 def test_both_sorts_at_their_line(case):
     test_shared_prefixes(case)
 
