@@ -138,3 +138,41 @@ def test_close_that_cannot_wait_keeps_the_table(monkeypatch):
     S.check_ok()
     assert ids.tolist() == [[1, 10, 3, 11]]
     t.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["none", "stream", "handle", "zero", "default", "external"])
+def test_streams_by_handle_and_object(kind):
+    """The build's and the precompute's memory is ordered on the stream that the
+    call runs on, however that is named, with work queued there before it."""
+    from test_gpu_fgram_model import bf16_dev
+    from workloads.fgram_model import ModelConfig, make_params, make_token_rows
+    side = torch.cuda.Stream()
+    stream = {"none": None, "stream": side, "handle": side.cuda_stream, "zero": 0,
+              "default": torch.cuda.default_stream(),
+              "external": torch.cuda.ExternalStream(side.cuda_stream)}[kind]
+    rng = np.random.default_rng(3)
+    fg, ln = all_ngrams([0, 1, 9, 40], 5, 0.6, rng)
+    ids = (50 + np.arange(len(ln))).astype(np.int32)
+    t = [dev(fg), dev(ln), dev(ids)]
+    X = rng.choice([0, 1, 9, 40], size=(3, 200)).astype(np.int32)
+    want, _ = oracle.OracleTable(fg, ln, ids).lookup(X, 5)
+    cfg = ModelConfig(512, 8, 128, 1, 5)
+    model = S.FgramModel(make_params(cfg, seed=1), 512, 8, 128, 1, 5)
+    tok = bf16_dev(make_token_rows(50, 512, seed=2))
+    rows = [torch.zeros((50 + len(ln), 512), dtype=torch.bfloat16, device="cuda")
+            for _ in range(2)]
+    S.precompute_fgram_rows(model, *t, tok, rows[0])
+    torch.cuda.synchronize()
+    for _ in range(3):
+        with torch.cuda.stream(side):           # freed blocks that are still being written
+            for _ in range(20):
+                torch.empty(1 << 22, dtype=torch.uint8, device="cuda").fill_(255)
+        table = S.build_fgram_table(*t, stream=stream)
+        got, _ = S.lookup(table, dev(X), 5)
+        assert np.array_equal(got.cpu().numpy(), want)
+        rows[1].zero_()
+        torch.cuda.current_stream().synchronize()
+        S.precompute_fgram_rows(model, *t, tok, rows[1], stream=stream)
+        assert torch.equal(rows[0].view(torch.int16), rows[1].view(torch.int16))
+        table.close()
